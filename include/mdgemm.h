@@ -76,6 +76,7 @@ extern "C" {
 #define MDGEMM_STAGED 64u      /* always the staged kernels, never the fused small-product kernel (see below) */
 #define MDGEMM_GROUP_SIGN 128u      /* section 3's sign groups: A = A+ + A-, B likewise, four products (see below) */
 #define MDGEMM_GROUP_EXPONENT 256u  /* section 3's exponent classes over range_bits (see below) */
+#define MDGEMM_WORKSPACE_SCRATCH 512u       /* the caller workspace's contents are not read afterwards (see below) */
 
 /* cutoff selectors for mdgemm_opts.cutoff (else an explicit T in 0 .. 2S-2) */
 #define MDGEMM_CUTOFF_DEFAULT -1  /* T = S - 1: the pair set of the rewritten product */
@@ -88,7 +89,7 @@ typedef struct mdgemm_opts {
   int slices_per_limb;    /* 13-bit digits per limb, S = limbs * slices_per_limb; 0 = the default count (below) */
   int cutoff;             /* largest kept p + q; MDGEMM_CUTOFF_DEFAULT or _ALL or 0..2S-2 */
   unsigned flags;         /* MDGEMM_CHECK_FINITE, _SYNC, _TIME_STAGES, _KARATSUBA, _KARATSUBA_MIN_TERMS, _INT8,
-                             _STAGED, _GROUP_SIGN, _GROUP_EXPONENT */
+                             _STAGED, _GROUP_SIGN, _GROUP_EXPONENT, _WORKSPACE_SCRATCH */
   int slice_bits;         /* digit width w: 0 = 13 (section 2), 1..26, or MDGEMM_SLICE_BITS_AUTO */
   int slices;             /* digits per element S; 0 = derived (see below) */
   int range_bits;         /* range balancing: full precision down to 2^-range_bits of the line; 0 = off */
@@ -99,7 +100,14 @@ typedef struct mdgemm_opts {
  * device, grown on demand: calls that use it are ordered among themselves on the
  * GPU (each waits for the previous user's work, across streams), and such a call
  * is refused with MDGEMM_EINVAL while its stream is capturing a graph (the graph
- * would keep an address that a later, larger call may free). */
+ * would keep an address that a later, larger call may free).
+ * MDGEMM_WORKSPACE_SCRATCH declares that nothing in the caller workspace is read
+ * after the call (mdgemm_workspace_layout does not describe it then).  As in the
+ * library's own buffer, the products may then run on the int8 matrix cores
+ * whatever the digit width (see "Products on the int8 matrix cores" below), several
+ * times faster for all but small products; mdgemm_workspace_bytes with the flag
+ * gives the bytes for that, and a smaller workspace that is large enough without
+ * the flag still works, without them. */
 
 /* Digit width and count.
  *  - The default count of 13-bit digits, S13(L): four per limb up to quad
@@ -182,12 +190,23 @@ typedef struct mdgemm_opts {
  * MDGEMM_CHECK_FINITE; MDGEMM_STAGED turns it off.  With MDGEMM_TIME_STAGES the
  * whole kernel counts as the level-product stage. */
 
+/* Products on the int8 matrix cores.  The levels only enter the exact sum
+ * Z = sum_t G_t 2^(-w t), so any exact way of forming that sum gives the same
+ * limbs.  Where no intermediate result can be read afterwards (the library's
+ * buffer, the array of mdgemm_ex_noalloc, a workspace with
+ * MDGEMM_WORKSPACE_SCRATCH) and its estimated time is lower, the kept digit pairs
+ * are covered by rectangles, each formed modulo coprime integers of at most 8 bits
+ * with one int8 product per modulus and recovered by the Chinese remainder theorem,
+ * or, for single pairs, by Karatsuba's identity on 7-bit sub-digits: every limb
+ * equals that of the FP64 level products.  Not with MDGEMM_STAGED, MDGEMM_INT8,
+ * MDGEMM_KARATSUBA_MIN_TERMS or the grouped products, nor for k above 2^15. */
+
 /* Logging.  With the environment variable MDGEMM_LOG=1 (read once per process)
  * every call of mdgemm, mdgemm_ex, mdgemm_ex_noalloc and mdgemm_qr_dd writes one
  * line to stderr when it returns: its sizes, the plan (w, S, T; "unplanned" for
  * arguments that do not resolve), the flags, the workspace kind, the stream, the
- * path taken (refused, empty, zero (k = 0), fused small product, staged: pair
- * levels / karatsuba / grouped products, int8 levels) and the status string.
+ * path taken (refused, empty, zero (k = 0), fused small product, int8 residues,
+ * staged: pair levels / karatsuba / grouped products, int8 levels) and the status string.
  * MDGEMM_LOG=2 also logs the products a QR makes.  Unset or 0: silent. */
 
 /* Fill `opts` with the defaults: default stream, library workspace, the default

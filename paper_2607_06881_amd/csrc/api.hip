@@ -452,7 +452,7 @@ double staged_estimate_us(int64_t m, int64_t n, int64_t k, int T, int heaviest_p
 }
 
 bool small_plan(int64_t m, int64_t n, int64_t k, int limbs, const Resolved& r, int* kc_out,
-                mdg::SmallLevelOwners* owners) {
+                mdg::SmallLevelOwners* owners, double* fused_us = nullptr) {
   if (r.kind == Kind::kGroups ||
       (r.flags & (MDGEMM_INT8 | MDGEMM_KARATSUBA | MDGEMM_KARATSUBA_MIN_TERMS | MDGEMM_STAGED | MDGEMM_CHECK_FINITE)))
     return false;
@@ -485,11 +485,63 @@ bool small_plan(int64_t m, int64_t n, int64_t k, int limbs, const Resolved& r, i
     total += bp;
   }
   const int maxload = std::max(std::max(load[0], load[1]), std::max(load[2], load[3]));
-  if (fused_estimate_us(k, limbs, r.S, maxload) > staged_estimate_us(m, n, k, r.T, heaviest, total)) return false;
+  const double us = fused_estimate_us(k, limbs, r.S, maxload);
+  if (us > staged_estimate_us(m, n, k, r.T, heaviest, total)) return false;
+  if (fused_us) *fused_us = us;
   int kc = static_cast<int>(std::min<int64_t>(256, (k + 3) / 4 * 4));
   while (kc > 4 && mdg::small_product_lds(r.S, r.T, kc) > mdg::kSmallMaxLds) kc -= 4;
   if (mdg::small_product_lds(r.S, r.T, kc) > mdg::kSmallMaxLds) return false;
   *kc_out = kc;
+  return true;
+}
+
+// The int8 products of modular.h in place of the FP64 level GEMM: the same exact
+// sum of the kept digit pairs, so the same limbs, where nothing but C is read
+// afterwards (scratch: the library's buffer, the fixed scratch array, or a caller
+// workspace marked MDGEMM_WORKSPACE_SCRATCH) and the estimated time is below that
+// of the path that would run otherwise.  Not with MDGEMM_STAGED, the shortest
+// Karatsuba schedule, grouped or int8-digit products.
+constexpr double kModularBaseUs = 48.0;  // its six launches and their gaps
+std::shared_ptr<const mdg::ModPlan> modular_for(int64_t m, int64_t n, int64_t k, int limbs, const Resolved& r,
+                                                bool scratch) {
+  if (!scratch || (r.kind != Kind::kLevels && r.kind != Kind::kKaratsuba) ||
+      (r.flags & (MDGEMM_INT8 | MDGEMM_STAGED | MDGEMM_KARATSUBA_MIN_TERMS)) || r.Ge > 1 || r.sign)
+    return nullptr;
+  if (mdg::accum_words(r.T + 1, r.w) > mdg::kModMaxWords || m > (int64_t{1} << 27) || n > (int64_t{1} << 27))
+    return nullptr;
+  auto pl = mdg::modular_plan(m, n, k, r.S, r.T, r.w);
+  if (!pl || !mdg::modular_gemm_fits(mdg::mod_kp(k), pl->pa) || !mdg::modular_gemm_fits(mdg::mod_kp(k), pl->pb))
+    return nullptr;
+  int kc = 0;
+  mdg::SmallLevelOwners owners{};
+  double us = 0.0;
+  if (!small_plan(m, n, k, limbs, r, &kc, &owners, &us))
+    us = staged_estimate_us(m, n, k, r.T, max_pairs(r.S, r.T), pair_count(r.S, r.T));
+  return kModularBaseUs + 1e6 * pl->seconds < us ? pl : nullptr;
+}
+
+// EA | EB | A's panels | B's panels | output planes, each aligned to 256 bytes.
+struct LayoutMod {
+  size_t ea = 0, eb = 0, da = 0, db = 0, p = 0, total = 0;
+};
+bool layout_modular(int64_t m, int64_t n, int64_t k, const mdg::ModPlan& pl, LayoutMod* L) {
+  const double kp = static_cast<double>(mdg::mod_kp(k));
+  if (kp * ((double)pl.pa * (m + 256.0) + (double)pl.pb * (n + 256.0)) + 4.0 * pl.planes * (m + 3.0) * n > 4.0e18)
+    return false;
+  const size_t kpz = static_cast<size_t>(mdg::mod_kp(k));
+  size_t off = 0;
+  L->ea = off;
+  off += align_up(sizeof(int32_t) * static_cast<size_t>(m));
+  L->eb = off;
+  off += align_up(sizeof(int32_t) * static_cast<size_t>(n));
+  L->da = off;
+  off += align_up(kpz * static_cast<size_t>(pl.pa) * static_cast<size_t>(mdg::mod_rows(m)));
+  L->db = off;
+  off += align_up(kpz * static_cast<size_t>(pl.pb) * static_cast<size_t>(mdg::mod_rows(n)));
+  L->p = off;
+  off += align_up(sizeof(uint32_t) * static_cast<size_t>(pl.planes) * static_cast<size_t>(mdg::mod_quads(m)) *
+                  static_cast<size_t>(n));
+  L->total = off;
   return true;
 }
 
@@ -814,6 +866,40 @@ int run_int8(int64_t m, int64_t n, int64_t k, int limbs, const double* A, const 
   return MDGEMM_OK;
 }
 
+// The product by the int8 products of a plan, in a workspace laid out by
+// layout_modular (m, n, k > 0, arguments checked).
+int enqueue_modular(int64_t m, int64_t n, int64_t k, int limbs, const double* A, const double* B, double* C,
+                    const Resolved& r, const mdg::ModPlan& pl, const LayoutMod& L, char* ws) {
+  hipStream_t s = r.stream;
+  const bool timed = (r.flags & MDGEMM_TIME_STAGES) != 0;
+  int32_t* EA = reinterpret_cast<int32_t*>(ws + L.ea);
+  int32_t* EB = reinterpret_cast<int32_t*>(ws + L.eb);
+  int8_t* DA = reinterpret_cast<int8_t*>(ws + L.da);
+  int8_t* DB = reinterpret_cast<int8_t*>(ws + L.db);
+  uint32_t* P = reinterpret_cast<uint32_t*>(ws + L.p);
+  if (r.flags & MDGEMM_CHECK_FINITE) MDG_TRY(check_finite(m, n, k, limbs, A, B, EA, s));
+  std::unique_lock<std::mutex> tlock(timing().mu, std::defer_lock);
+  if (timed) {
+    tlock.lock();
+    timing().valid = false;
+    MDG_TRY(record(0, s));
+  }
+  // the partial column maxima go through the planes' region, written later
+  MDG_TRY(hip_status(mdg::launch_exponents_ab(m, k, n, A, B, EA, EB, P, L.total - L.p, s)));
+  if (timed) MDG_TRY(record(1, s));
+  MDG_TRY(hip_status(mdg::launch_modular_split(m, k, limbs, r.S, r.w, 0, A, EA, DA, pl, s)));
+  MDG_TRY(hip_status(mdg::launch_modular_split(k, n, limbs, r.S, r.w, 1, B, EB, DB, pl, s)));
+  if (timed) MDG_TRY(record(2, s));
+  MDG_TRY(hip_status(mdg::launch_modular_gemm(m, n, mdg::mod_kp(k), pl, DA, DB, P, s)));
+  if (timed) MDG_TRY(record(3, s));
+  MDG_TRY(hip_status(mdg::launch_modular_accum(m, n, limbs, r.T, r.w, pl, P, EA, EB, C, s)));
+  if (timed) {
+    MDG_TRY(record(4, s));
+    timing().valid = true;
+  }
+  return MDGEMM_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -860,6 +946,11 @@ size_t mdgemm_workspace_bytes(int64_t m, int64_t n, int64_t k, int limbs, const 
   if (r.flags & MDGEMM_INT8) {
     LayoutI8 L8;
     return layout_int8(m, n, k, r.S, r.T, &L8) ? L8.total : SIZE_MAX;
+  }
+  if (r.flags & MDGEMM_WORKSPACE_SCRATCH) {
+    LayoutMod lm;
+    const auto mod = resolved_exact(r, k) ? modular_for(m, n, k, limbs, r, true) : nullptr;
+    if (mod && layout_modular(m, n, k, *mod, &lm)) return lm.total;
   }
   Layout L;
   if (!layout(m, n, k, *planned_for(r.S, r.T, m, n, k, r.w, r.kind, group_code(r)), r.w, &L)) return SIZE_MAX;
@@ -929,6 +1020,30 @@ int ex_impl(int64_t m, int64_t n, int64_t k, int limbs, const double* A, const d
   if (r.flags & MDGEMM_INT8) {
     *path = "int8 levels";
     return run_int8(m, n, k, limbs, A, B, C, opts, r);
+  }
+  // the int8 products, when the workspace is scratch and holds them (else the
+  // paths below, in the workspace they always took)
+  const bool caller_ws = opts && opts->workspace;
+  const auto mod = modular_for(m, n, k, limbs, r, !caller_ws || (r.flags & MDGEMM_WORKSPACE_SCRATCH));
+  LayoutMod lm;
+  if (mod && layout_modular(m, n, k, *mod, &lm) && (!caller_ws || opts->workspace_bytes >= lm.total)) {
+    *path = "int8 residues";
+    char* ws = nullptr;
+    LibraryBuffer lib;
+    int st = MDGEMM_OK;
+    if (caller_ws) {
+      if (workspace_overlaps(opts->workspace, lm.total, m, n, k, limbs, A, B, C)) return MDGEMM_EINVAL;
+      ws = static_cast<char*>(opts->workspace);
+    } else {
+      st = lib.acquire(lm.total, s, &ws);
+    }
+    if (st == MDGEMM_OK) {
+      MDG_TRY(lib.release(enqueue_modular(m, n, k, limbs, A, B, C, r, *mod, lm, ws)));
+      if (r.flags & MDGEMM_SYNC) MDG_TRY(hip_status(hipStreamSynchronize(s)));
+      return MDGEMM_OK;
+    }
+    if (st != MDGEMM_ENOMEM && st != MDGEMM_EINVAL) return st;  // no room, or capturing: the paths below
+    *path = "refused";
   }
   const auto pl = planned_for(r.S, r.T, m, n, k, r.w, r.kind, group_code(r));
   if (!schedule_exact(pl->s, k, r.w)) return MDGEMM_EEXACT;
@@ -1028,7 +1143,7 @@ void log_product(const char* entry, int64_t m, int64_t n, int64_t k, int limbs, 
                  const char* ws, const char* path, int status) {
   int w = 0, S = 0, T = 0;
   const bool planned = mdgemm_plan(m, n, k, limbs, opts, &w, &S, &T) == MDGEMM_OK;
-  const unsigned flags = opts ? opts->flags : 0u;
+  const unsigned flags = opts ? opts->flags & ~MDGEMM_WORKSPACE_SCRATCH : 0u;
   char plan[64] = "unplanned";
   if (planned) std::snprintf(plan, sizeof plan, "w=%d S=%d T=%d", w, S, T);
   mdg::log_line("%s m=%lld n=%lld k=%lld limbs=%d %s flags=0x%x workspace=%s stream=%p path=%s -> %s", entry,
@@ -1068,7 +1183,10 @@ int mdgemm_ex(int64_t m, int64_t n, int64_t k, int limbs, const double* A, const
   const char* path = "refused";
   const int st = ex_impl(m, n, k, limbs, A, B, C, opts, &path);
   if (mdg::log_level() > mdg::log_depth)
-    log_product("mdgemm_ex", m, n, k, limbs, opts, opts && opts->workspace ? "caller" : "library", path, st);
+    log_product("mdgemm_ex", m, n, k, limbs, opts,
+                !opts || !opts->workspace ? "library"
+                : (opts->flags & MDGEMM_WORKSPACE_SCRATCH) ? "caller (scratch)" : "caller",
+                path, st);
   return st;
 }
 
@@ -1137,6 +1255,7 @@ int noalloc_impl(int64_t m, int64_t n, int64_t k, int limbs, const double* A, co
   MDG_TRY(noalloc_scratch(&p));
   o.workspace = p;
   o.workspace_bytes = MDGEMM_NOALLOC_MAX_BYTES;
+  o.flags |= MDGEMM_WORKSPACE_SCRATCH;
   return ex_impl(m, n, k, limbs, A, B, C, &o, path);
 }
 

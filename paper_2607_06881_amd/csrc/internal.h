@@ -7,6 +7,7 @@
 
 #include <vector>
 
+#include "modular.h"
 #include "schedule.h"
 
 namespace mdg {
@@ -116,6 +117,18 @@ hipError_t launch_split_int8t(int64_t rows, int64_t cols, int L, int S, int w, c
 bool level_gemm_i8_fits(int64_t kp, int S);
 hipError_t launch_level_gemm_i8(int64_t m, int64_t n, int64_t kp, int S, int T, const int8_t* DA, const int8_t* DBt,
                                 int32_t* G, hipStream_t stream);
+
+// The int8 products of a plan (modular.h): a2, the panels of A (axis 0, pl.a: rows
+// of pl.pa panels) or B (axis 1, pl.b), mod_kp(k) bytes each, mod_rows() rows of
+// memory; a3, the output planes P (4 pl.planes mod_quads(m) n bytes, 16-byte
+// aligned); a4 + a5 from the planes.
+hipError_t launch_modular_split(int64_t rows, int64_t cols, int L, int S, int w, int axis, const double* X,
+                                const int32_t* E, int8_t* D, const ModPlan& pl, hipStream_t stream);
+bool modular_gemm_fits(int64_t kp, int panels);
+hipError_t launch_modular_gemm(int64_t m, int64_t n, int64_t kp, const ModPlan& pl, const int8_t* DA, const int8_t* DB,
+                               uint32_t* P, hipStream_t stream);
+hipError_t launch_modular_accum(int64_t m, int64_t n, int L, int T, int w, const ModPlan& pl, const uint32_t* P,
+                                const int32_t* EA, const int32_t* EB, double* C, hipStream_t stream);
 
 // a3: products of the combination panels DAt [*][panel_k(k)][panel_mn(m)] and
 // DBp [*][panel_k(k)][panel_mn(n)] (combinations 0..S-1 are the digits); one

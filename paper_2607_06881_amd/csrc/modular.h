@@ -1,0 +1,94 @@
+// Level products on the int8 matrix cores by blocks of digit pairs.
+//
+// The product of an element pair is Z = sum over the kept digit pairs (p, q) of
+// DA_p DB_q 2^(-w (p + q)), summed over k: a sum of integers, so any exact way
+// of forming it gives the same limbs.  The kept pairs are covered by disjoint
+// rectangles [p0, p0 + u) x [q0, q0 + v).  The digits of a rectangle are one
+// signed integer per element, a = sum of DA_p 2^(w (p1 - p)) of w u bits, b of
+// w v bits, and the rectangle contributes V 2^(-w (p1 + q1)) with V = sum_k a b.
+//  - Residue groups: V is formed modulo N pairwise coprime moduli of at most 8
+//    bits, one int8 product each (operands the balanced residues of a and b), and
+//    recovered by the Chinese remainder theorem: V = sum_i y_i W_i - q M with
+//    W_i = M / m_i and y_i = V W_i^-1 mod m_i (the factor W_i^-1 is folded into
+//    A's residues, so the product's residue is y_i itself).  N grows with the
+//    bits of V, w (u + v) + log2 k, while the pairs covered grow with u v: eight
+//    by eight 13-bit digits take 29 products instead of 192.
+//  - Direct groups: single pairs of one level, by sub-digits of 7 bits
+//    (balanced, base 128) and Karatsuba's identity on them: c = ceil((w + 1) / 7)
+//    sub-digits take c (c + 1) / 2 products (3 for 13-bit digits, against 6 or 7
+//    residues), each summed in int32 over the level's pairs.
+// Rectangles (or pairs) with the same p1 + q1 and bits share a group: their
+// products are summed over a longer k range.
+#pragma once
+
+#include <stdint.h>
+
+#include <memory>
+#include <vector>
+
+namespace mdg {
+
+constexpr int kMaxModuli = 40;  // 291 bits; the next ones hold less than 6.2 bits
+constexpr int kModLimbs = 12;   // 32-bit limbs of the product of all moduli, in whole chunks of four
+constexpr int kModMaxBlocks = 136;
+constexpr int kModMaxPanels = 512;
+constexpr int kModMaxGroups = 136;
+constexpr int kModMaxJobs = 320;
+constexpr int kDirectTypes = 10;  // sub-digit products of a digit pair (4 sub-digits)
+constexpr int kModMaxBits = 192;  // integer of a residue block
+constexpr int kModTile = 256;     // output tile edge of the int8 products
+constexpr int kModStage = 128;    // bytes of k per LDS stage
+
+// The largest pairwise coprime integers up to 256, greedily from 256 down.
+constexpr int kModuli[kMaxModuli] = {256, 255, 253, 251, 247, 241, 239, 233, 229, 227, 223, 217, 211, 199,
+                                     197, 193, 191, 181, 179, 173, 167, 163, 157, 151, 149, 139, 137, 131,
+                                     127, 113, 109, 107, 103, 101, 97,  89,  83,  79,  73,  71};
+
+// Digits p0 .. p0 + u - 1 of an operand as one integer: bits lo .. lo + bits - 1
+// of D; `count` int8 panels are made from it: residues modulo the first `count`
+// moduli (residue, with the factors of the `count`-moduli system folded in when
+// scaled), or the sub-digit types of one digit (direct).
+struct ModBlock {
+  uint16_t lo;
+  uint8_t bits, count, residue, scaled;
+};
+
+// One int8 product: panels a + i da of A times b + i db of B, i < nseg, summed;
+// residue jobs (mod < kMaxModuli) store y as one byte, direct ones int32; out in
+// units of one dword per four rows.
+struct ModJob {
+  uint16_t a, b;
+  int16_t da, db;
+  uint16_t nseg, mod, out;
+};
+constexpr int kDirectJob = 255;
+
+// Output planes out .. of a group and the weight 2^shift of its value V in the
+// accumulated integer N = sum_t G_t 2^(w (T - t)).
+struct ModGroup {
+  uint16_t shift, out;
+  uint8_t residue, count;
+};
+
+struct ModPlan {
+  std::vector<ModBlock> a, b;
+  std::vector<ModJob> jobs;
+  std::vector<ModGroup> groups;
+  int pa = 0, pb = 0;    // panels of A and of B
+  int planes = 0;        // dwords per four rows of all output planes
+  int direct_bits = 0;   // w
+  int64_t products = 0;  // int8 products of length k
+  double seconds = 0.0;  // estimated time, for choosing the path
+};
+
+// The plan for the digit pairs p + q <= T of S digits of w bits and an m x k by
+// k x n product; nullptr when none fits the limits above (or the int32 sums).
+std::shared_ptr<const ModPlan> modular_plan(int64_t m, int64_t n, int64_t k, int S, int T, int w);
+
+constexpr int kModMaxWords = 15;  // 64-bit words of the accumulated integer
+
+inline int64_t mod_kp(int64_t k) { return (k + kModStage - 1) / kModStage * kModStage; }
+inline int64_t mod_rows(int64_t x) { return (x + kModTile - 1) / kModTile * kModTile; }
+inline int64_t mod_quads(int64_t m) { return (m + 3) / 4; }
+
+}  // namespace mdg

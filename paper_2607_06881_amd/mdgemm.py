@@ -35,6 +35,7 @@ MDGEMM_INT8 = 32
 MDGEMM_STAGED = 64
 MDGEMM_GROUP_SIGN = 128
 MDGEMM_GROUP_EXPONENT = 256
+MDGEMM_WORKSPACE_SCRATCH = 512
 MDGEMM_SCHEDULE_INFO = 12
 MDGEMM_LAYOUT_INFO = 12
 MDGEMM_NOALLOC_MAX_BYTES = 64 << 20
@@ -280,8 +281,8 @@ def mdgemm_ex(A: torch.Tensor, B: torch.Tensor, C: Optional[torch.Tensor] = None
               stream=None, slice_bits: int = 0, slices: int = 0, range_bits: int = 0) -> torch.Tensor:
     """C = A.B for limb-major float64 tensors A [L, m, k] and B [L, k, n] on the GPU.
 
-    The workspace is a torch uint8 tensor (allocated here when not given), so
-    device memory comes from PyTorch's allocator."""
+    The workspace is a torch uint8 tensor (allocated here when not given, and then
+    scratch: MDGEMM_WORKSPACE_SCRATCH), so device memory comes from PyTorch's allocator."""
     _dev_tensor(A, torch.float64, "A")
     _dev_tensor(B, torch.float64, "B")
     if A.dim() != 3 or B.dim() != 3 or A.shape[0] != B.shape[0] or A.shape[2] != B.shape[1]:
@@ -295,6 +296,7 @@ def mdgemm_ex(A: torch.Tensor, B: torch.Tensor, C: Optional[torch.Tensor] = None
         if tuple(C.shape) != (L, m, n):
             raise ValueError("C has the wrong shape")
     if workspace is None:
+        flags |= MDGEMM_WORKSPACE_SCRATCH
         need = mdgemm_workspace_bytes(m, n, k, L, slices_per_limb=slices_per_limb, cutoff=cutoff,
                                       slice_bits=slice_bits, slices=slices, range_bits=range_bits, flags=flags)
         if need == 2**64 - 1:

@@ -1,0 +1,137 @@
+"""Products on the int8 matrix cores by residues and sub-digits, whatever the digit width.
+
+Every limb must equal that of the FP64 level products (MDGEMM_STAGED), which the other
+GPU tests pin against the oracle; some of these products are checked against the oracle
+directly.  The results are roundings of exact integers, so the comparison is bit for bit.
+The sizes cover the edges of the 256 x 256 tiles, of the 128-byte k stages and of the
+rows of four that the planes hold; the options cover every sub-digit count, residue
+systems of one to three limb chunks, and the word counts of the accumulation.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import pipeline
+from paper_2607_06881_amd import mdgemm as md
+from paper_2607_06881_amd import workloads
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+ALL = md.MDGEMM_CUTOFF_ALL
+
+
+def _modular(m, n, k, L, **opts):
+    """True when the library takes the int8 products (their workspace differs)."""
+    flags = opts.pop("flags", 0)
+    return (md.mdgemm_workspace_bytes(m, n, k, L, flags=flags | md.MDGEMM_WORKSPACE_SCRATCH, **opts)
+            != md.mdgemm_workspace_bytes(m, n, k, L, flags=flags, **opts))
+
+
+def _operands(L, m, n, k, seed, spread=0):
+    rng = np.random.default_rng(seed)
+    A = workloads.make_operand(rng, L, m, k, "normal", row_exp=20, elem_exp=spread)
+    B = workloads.make_operand(rng, L, k, n, "normal", col_exp=20, elem_exp=spread)
+    A[:, 0, :] = 0.0  # an all-zero line of each operand, and single zeros
+    B[:, :, n - 1] = 0.0
+    A[:, m - 1, k // 2] = 0.0
+    return torch.from_numpy(A).to(DEV), torch.from_numpy(B).to(DEV)
+
+
+CASES = [
+    # limbs, m, n, k, options
+    (2, 255, 257, 127, {}),
+    (2, 256, 512, 128, {}),
+    (2, 257, 511, 129, {}),
+    (2, 513, 258, 1, {}),
+    (2, 301, 303, 640, {"cutoff": ALL}),
+    (1, 511, 301, 260, {}),
+    (3, 259, 300, 257, {}),
+    (3, 300, 260, 130, {"cutoff": ALL}),
+    (4, 262, 290, 200, {}),
+    (4, 300, 300, 100, {"cutoff": ALL}),
+    (8, 258, 300, 70, {}),
+    (16, 258, 264, 40, {}),
+    (2, 300, 300, 300, {"range_bits": 60}),
+    (2, 300, 300, 300, {"slice_bits": -1}),
+    (2, 1500, 1500, 100, {"slice_bits": 22}),
+    (3, 700, 700, 200, {"slice_bits": 21, "cutoff": ALL}),
+    (2, 300, 300, 90, {"slice_bits": 20}),
+    (2, 300, 300, 90, {"slice_bits": 7, "slices": 16}),
+    (1, 300, 300, 90, {"slice_bits": 5}),
+    (2, 300, 300, 200, {"flags": md.MDGEMM_KARATSUBA}),
+    (2, 300, 300, 200, {"cutoff": 3}),
+    (2, 70, 4000, 300, {}),
+    (2, 4100, 40, 300, {}),
+]
+
+
+@pytest.mark.parametrize("L,m,n,k,opts", CASES)
+def test_limbs_equal_the_fp64_level_products(L, m, n, k, opts):
+    print(f"[case] L={L} {m}x{n}x{k} {opts}", flush=True)
+    assert _modular(m, n, k, L, **opts)
+    A, B = _operands(L, m, n, k, 5 * m + k, spread=6)
+    plain = {x: y for x, y in opts.items() if x != "flags"}
+    want = md.mdgemm_ex(A, B, flags=md.MDGEMM_STAGED, **plain)
+    got = md.mdgemm_ex(A, B, **opts)
+    assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("L,m,n,k,opts", [(2, 260, 258, 130, {}), (4, 257, 300, 33, {"cutoff": ALL})])
+def test_limbs_equal_the_oracle(L, m, n, k, opts):
+    print(f"[case] oracle L={L} {m}x{n}x{k} {opts}", flush=True)
+    assert _modular(m, n, k, L, **opts)
+    A, B = _operands(L, m, n, k, 11)
+    got = md.mdgemm_ex(A, B, **opts).cpu().numpy()
+    _, S, T = md.mdgemm_plan(m, n, k, L, **opts)
+    rows = [0, 1, m // 2, m - 2, m - 1]
+    ref = pipeline.full_reference(A.cpu().numpy()[:, rows], B.cpu().numpy(), S, T)["C"]
+    assert np.array_equal(got[:, rows], ref)
+
+
+@pytest.mark.parametrize("m,n,k,opts", [(260, 258, 512, {}), (260, 258, 512, {"cutoff": ALL}),
+                                        (260, 258, 512, {"slice_bits": 20}), (1000, 1000, 400, {"slice_bits": 21})])
+def test_largest_digits_of_either_sign(m, n, k, opts):
+    """Every digit at its largest magnitude: the sums reach their bounds."""
+    print(f"[case] largest digits {m}x{n}x{k} {opts}", flush=True)
+    A = np.full((2, m, k), 1.0 - 2.0 ** -53)
+    A[1] = 2.0 ** -54 * (1.0 - 2.0 ** -53)
+    B = np.full((2, k, n), 1.0 - 2.0 ** -53)
+    B[1] = 2.0 ** -54 * (1.0 - 2.0 ** -53)
+    A[:, ::2] *= -1.0
+    B[:, :, ::3] *= -1.0
+    Ag, Bg = torch.from_numpy(A).to(DEV), torch.from_numpy(B).to(DEV)
+    assert _modular(m, n, k, 2, **opts)
+    assert torch.equal(md.mdgemm_ex(Ag, Bg, **opts), md.mdgemm_ex(Ag, Bg, flags=md.MDGEMM_STAGED, **opts))
+
+
+def test_library_buffer_capture_and_a_small_workspace():
+    m, n, k, L = 300, 280, 150, 2
+    A, B = _operands(L, m, n, k, 3)
+    want = md.mdgemm_ex(A, B, flags=md.MDGEMM_STAGED)
+    assert torch.equal(md.mdgemm(A, B), want)  # the library's buffer
+    # a workspace that only the FP64 path fits is still taken
+    need = md.mdgemm_workspace_bytes(m, n, k, L)
+    ws = torch.empty(need, dtype=torch.uint8, device=DEV)
+    assert torch.equal(md.mdgemm_ex(A, B, workspace=ws, flags=md.MDGEMM_WORKSPACE_SCRATCH), want)
+    full = md.mdgemm_workspace_bytes(m, n, k, L, flags=md.MDGEMM_WORKSPACE_SCRATCH)
+    ws = torch.empty(full, dtype=torch.uint8, device=DEV)
+    C = torch.empty_like(want)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        md.mdgemm_ex(A, B, C, workspace=ws, flags=md.MDGEMM_WORKSPACE_SCRATCH)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            md.mdgemm_ex(A, B, C, workspace=ws, flags=md.MDGEMM_WORKSPACE_SCRATCH)
+    torch.cuda.current_stream().wait_stream(side)
+    for rep in range(3):
+        print(f"[case] graph replay {rep}", flush=True)
+        A2, B2 = _operands(L, m, n, k, 20 + rep)
+        A.copy_(A2)
+        B.copy_(B2)
+        C.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(C, md.mdgemm_ex(A, B, flags=md.MDGEMM_STAGED))
