@@ -29,7 +29,7 @@
 namespace mdg {
 
 constexpr int kMaxModuli = 40;  // 291 bits; the next ones hold less than 6.2 bits
-constexpr int kModLimbs = 12;   // 32-bit limbs of the product of all moduli, in whole chunks of four
+constexpr int kModLimbs = 10;   // 32-bit limbs of the product of all moduli
 constexpr int kModMaxBlocks = 136;
 constexpr int kModMaxPanels = 512;
 constexpr int kModMaxGroups = 136;

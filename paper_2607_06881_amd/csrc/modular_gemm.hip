@@ -53,7 +53,7 @@ constexpr unsigned kWaitVmLgkm0 = 0x0070;  // s_waitcnt vmcnt(0) lgkmcnt(0)
 // the jobs of one launch: at most kJobsPerLaunch, longest first
 constexpr int kJobsPerLaunch = 160;
 struct Jobs {
-  ModJob j[kJobsPerLaunch];
+  uint32_t j[kJobsPerLaunch][4];  // a | b << 16, da | db << 16, nseg | mod << 16, out (whole dwords for scalar loads)
 };
 
 // the granule swizzle of LDS row r (depends on r mod 16 only)
@@ -184,7 +184,17 @@ __global__ void __launch_bounds__(512, 1) modular_gemm_kernel(int64_t m, int64_t
   const int rows_in = min(group, tiles_m - first), within = tt - g * gsz;
   const int64_t m0 = static_cast<int64_t>(first + within % rows_in) * kTile;
   const int64_t n0 = static_cast<int64_t>(within / rows_in) * kTile;
-  const ModJob job = jobs.j[blockIdx.y];
+  ModJob job;
+  {
+    const uint32_t w0 = jobs.j[blockIdx.y][0], w1 = jobs.j[blockIdx.y][1], w2 = jobs.j[blockIdx.y][2];
+    job.a = static_cast<uint16_t>(w0);
+    job.b = static_cast<uint16_t>(w0 >> 16);
+    job.da = static_cast<int16_t>(w1);
+    job.db = static_cast<int16_t>(w1 >> 16);
+    job.nseg = static_cast<uint16_t>(w2);
+    job.mod = static_cast<uint16_t>(w2 >> 16);
+    job.out = static_cast<uint16_t>(jobs.j[blockIdx.y][3]);
+  }
   const int spk = static_cast<int>(kp / kStage), nst = spk * job.nseg;
   Walk walk;
   walk.a = static_cast<uint32_t>(job.a * kp);
@@ -275,7 +285,13 @@ hipError_t launch_modular_gemm(int64_t m, int64_t n, int64_t kp, const ModPlan& 
   for (size_t first = 0; first < pl.jobs.size(); first += kJobsPerLaunch) {
     const size_t count = std::min<size_t>(kJobsPerLaunch, pl.jobs.size() - first);
     Jobs jobs{};
-    std::copy(pl.jobs.begin() + first, pl.jobs.begin() + first + count, jobs.j);
+    for (size_t i = 0; i < count; ++i) {
+      const ModJob& j = pl.jobs[first + i];
+      jobs.j[i][0] = j.a | static_cast<uint32_t>(j.b) << 16;
+      jobs.j[i][1] = static_cast<uint16_t>(j.da) | static_cast<uint32_t>(static_cast<uint16_t>(j.db)) << 16;
+      jobs.j[i][2] = j.nseg | static_cast<uint32_t>(j.mod) << 16;
+      jobs.j[i][3] = j.out;
+    }
     hipLaunchKernelGGL(modular_gemm_kernel, dim3(static_cast<unsigned>(ntiles), static_cast<unsigned>(count)),
                        dim3(512), 0, stream, m, n, kp, pl.pa * kp, pl.pb * kp, static_cast<int>(tiles_n),
                        static_cast<int>(ntiles), group, DA, DB, P, jobs);

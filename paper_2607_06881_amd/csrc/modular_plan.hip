@@ -98,6 +98,8 @@ class Coverer {
       for (int pass = 0; pass < 2; ++pass) {
         const int v = pass ? 1 : vmax;
         if (v < 1 || (pass && (vmax == 1 || u > 1))) continue;
+        // rectangles of several pairs reach the cutoff (their weight is then 1)
+        if (u + v > 2 && u + v - 2 != t) continue;
         const double c = rect_[static_cast<size_t>(u) * n_ + v] + cost(sa - u, v, t - u) + cost(sa, sb - v, t - v);
         if (c < best.cost) best = Cover{c, u, v};
       }

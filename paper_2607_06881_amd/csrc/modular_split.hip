@@ -29,10 +29,22 @@ namespace {
 
 constexpr int kLines = 16;
 
+__constant__ const ResidueTable kResidueTable = make_residue_table();
+
+// The blocks in one dword each (scalar loads need whole, aligned dwords).
 struct SplitBlocks {
   int count;
-  ModBlock b[kModMaxBlocks];
+  uint32_t b[kModMaxBlocks];
 };
+inline uint32_t pack_block(const ModBlock& b) {
+  return b.lo | static_cast<uint32_t>(b.bits) << 10 | static_cast<uint32_t>(b.count) << 18 |
+         static_cast<uint32_t>(b.residue) << 24 | static_cast<uint32_t>(b.scaled) << 25;
+}
+__device__ inline ModBlock unpack_block(uint32_t v) {
+  return ModBlock{static_cast<uint16_t>(v & 0x3ffu), static_cast<uint8_t>((v >> 10) & 0xffu),
+                  static_cast<uint8_t>((v >> 18) & 0x3fu), static_cast<uint8_t>((v >> 24) & 1u),
+                  static_cast<uint8_t>((v >> 25) & 1u)};
+}
 
 // 32 bits of the integer I starting at bit `lo` (uniform), by unrolled selects.
 template <int NW>
@@ -63,7 +75,7 @@ __device__ inline void residue_panels(const uint64_t (&I)[4][NW], const float (&
   }
   const int row = blk.scaled ? mod_row(blk.count, 0) : kModRows;
   for (int c = 0; c < blk.count; ++c) {
-    const uint32_t* t = kModTables.residue[row + c];
+    const uint32_t* t = kResidueTable.row[row + c];
     uint32_t k[ND];
 #pragma unroll
     for (int j = 0; j < ND; ++j) k[j] = t[j];
@@ -170,7 +182,7 @@ __global__ void __launch_bounds__(4 * TK) modular_split_kernel(int64_t lines, in
   }
   int8_t* out = D + c * ld + kk;
   for (int b = 0; b < blocks.count; ++b) {
-    const ModBlock blk = blocks.b[b];
+    const ModBlock blk = unpack_block(blocks.b[b]);
     if (blk.residue) {
       if (blk.bits <= 32) residue_panels<NW, 1>(I, sgn, blk, out, kp, store);
       else if (blk.bits <= 64) residue_panels<NW, 2>(I, sgn, blk, out, kp, store);
@@ -196,7 +208,7 @@ hipError_t launch_split_tile(int64_t lines, int64_t K, int64_t ls, int64_t ks, i
   if (blocks.size() > static_cast<size_t>(kModMaxBlocks) || panels > kModMaxPanels) return hipErrorInvalidValue;
   SplitBlocks sb;
   sb.count = static_cast<int>(blocks.size());
-  std::copy(blocks.begin(), blocks.end(), sb.b);
+  std::transform(blocks.begin(), blocks.end(), sb.b, pack_block);
   const size_t lds = sizeof(double) * static_cast<size_t>(L) * kLines * (TK + 2);
   const int64_t gx = (lines + kLines - 1) / kLines, gy = (kp + TK - 1) / TK;
   if (gy > 65535 || gx > 0x7fffffff) return hipErrorInvalidValue;
