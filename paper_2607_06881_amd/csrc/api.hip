@@ -887,8 +887,7 @@ int enqueue_modular(int64_t m, int64_t n, int64_t k, int limbs, const double* A,
   // the partial column maxima go through the planes' region, written later
   MDG_TRY(hip_status(mdg::launch_exponents_ab(m, k, n, A, B, EA, EB, P, L.total - L.p, s)));
   if (timed) MDG_TRY(record(1, s));
-  MDG_TRY(hip_status(mdg::launch_modular_split(m, k, limbs, r.S, r.w, 0, A, EA, DA, pl, s)));
-  MDG_TRY(hip_status(mdg::launch_modular_split(k, n, limbs, r.S, r.w, 1, B, EB, DB, pl, s)));
+  MDG_TRY(hip_status(mdg::launch_modular_split(m, n, k, limbs, r.S, r.w, A, B, EA, EB, DA, DB, pl, s)));
   if (timed) MDG_TRY(record(2, s));
   MDG_TRY(hip_status(mdg::launch_modular_gemm(m, n, mdg::mod_kp(k), pl, DA, DB, P, s)));
   if (timed) MDG_TRY(record(3, s));

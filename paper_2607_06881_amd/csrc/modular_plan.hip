@@ -114,8 +114,9 @@ class Coverer {
 
 int sub_digits(int w) { return w <= 7 ? 1 : (w + 7) / 7; }
 
-// The tables for one cover; false when a limit of the kernels does not hold.
-bool build(const std::vector<Rect>& rects, int64_t k, int S, int T, int w, ModPlan* pl) {
+// The tables for one cover, at most `longest` rectangles per job; false when a limit
+// of the kernels does not hold.
+bool build(const std::vector<Rect>& rects, int64_t longest, int64_t k, int S, int T, int w, ModPlan* pl) {
   const int c = sub_digits(w), types = c * (c + 1) / 2;
   // rectangles grouped by (direct or bits, p1 + q1), in order of p0
   std::map<std::tuple<int, int>, std::vector<Rect>> by;
@@ -174,7 +175,7 @@ bool build(const std::vector<Rect>& rects, int64_t k, int S, int T, int w, ModPl
     size_t i = 0;
     while (i < rs.size()) {
       // a run of rectangles whose panels advance by constant steps
-      const size_t most = std::min(rs.size(), i + static_cast<size_t>(std::min<int64_t>(room, 255)));
+      const size_t most = std::min(rs.size(), i + static_cast<size_t>(std::min<int64_t>(room, longest)));
       std::vector<Seg> segs;
       size_t j = i;
       int count = types;
@@ -235,10 +236,15 @@ bool build(const std::vector<Rect>& rects, int64_t k, int S, int T, int w, ModPl
 double estimate(const ModPlan& pl, int64_t m, int64_t n, int64_t k) {
   const double mt = static_cast<double>(mod_rows(m)), nt = static_cast<double>(mod_rows(n));
   const double mn = static_cast<double>(m) * static_cast<double>(n);
-  double s = 0.0;
-  for (const ModJob& j : pl.jobs)
-    s += mt * nt * (2.0 * static_cast<double>(mod_kp(k)) * j.nseg / kInt8Rate + kTileJob) +
-         mn * (j.mod == kDirectJob ? 8.0 / kPlaneRate : 2.0 / kPlaneRate + 0.3e-12);
+  // the products: the larger of all blocks spread over the CUs and the longest one
+  double s = 0.0, longest = 0.0;
+  for (const ModJob& j : pl.jobs) {
+    const double block = 2.0 * static_cast<double>(mod_kp(k)) * j.nseg / kInt8Rate + kTileJob;
+    s += mt * nt * block;
+    longest = std::max(longest, 256.0 * 65536.0 * block);
+  }
+  s = std::max(s, longest);
+  for (const ModJob& j : pl.jobs) s += mn * (j.mod == kDirectJob ? 8.0 / kPlaneRate : 2.0 / kPlaneRate + 0.3e-12);
   s += kPanelByte * static_cast<double>(k) * (static_cast<double>(m) * pl.pa + static_cast<double>(n) * pl.pb);
   return s;
 }
@@ -280,10 +286,14 @@ std::shared_ptr<const ModPlan> modular_plan(int64_t m, int64_t n, int64_t k, int
       for (int p = 0; p < S; ++p)
         for (int q = 0; q < S && p + q <= T; ++q) rects.push_back(Rect{p, q, 1, 1});
     }
-    auto pl = std::make_shared<ModPlan>();
-    if (!build(rects, kc, S, T, w, pl.get())) continue;
-    pl->seconds = estimate(*pl, mc, nc, kc);
-    if (!best || pl->seconds < best->seconds) best = pl;
+    // a level's pairs in one job, or at most two: where the launch leaves CUs idle the
+    // longest job is its time
+    for (int64_t longest : {int64_t{255}, int64_t{2}}) {
+      auto pl = std::make_shared<ModPlan>();
+      if (!build(rects, longest, kc, S, T, w, pl.get())) continue;
+      pl->seconds = estimate(*pl, mc, nc, kc);
+      if (!best || pl->seconds < best->seconds) best = pl;
+    }
   }
   std::lock_guard<std::mutex> lock(cache.mu);
   if (cache.map.size() > 4096) cache.map.clear();

@@ -17,6 +17,11 @@
 // lies in [-m/2, m/2]; the sign of the element multiplies it.  Bound by HBM
 // (8 L bytes read and one byte per panel written per element) together with about
 // nine vector operations per panel and element.
+//
+// Both operands go in one launch, and where that has fewer than 512 blocks, the
+// panels are shared out over up to eight blocks per tile (grid.z), each splitting
+// the tile again: a tile's panels are one serial chain of scalar loads and vector
+// work per wave (20 us per operand at 333 x 501 with one block per tile).
 #include <algorithm>
 
 #include "digits.h"
@@ -32,10 +37,6 @@ constexpr int kLines = 16;
 __constant__ const ResidueTable kResidueTable = make_residue_table();
 
 // The blocks in one dword each (scalar loads need whole, aligned dwords).
-struct SplitBlocks {
-  int count;
-  uint32_t b[kModMaxBlocks];
-};
 inline uint32_t pack_block(const ModBlock& b) {
   return b.lo | static_cast<uint32_t>(b.bits) << 10 | static_cast<uint32_t>(b.count) << 18 |
          static_cast<uint32_t>(b.residue) << 24 | static_cast<uint32_t>(b.scaled) << 25;
@@ -45,6 +46,20 @@ __device__ inline ModBlock unpack_block(uint32_t v) {
                   static_cast<uint8_t>((v >> 18) & 0x3fu), static_cast<uint8_t>((v >> 24) & 1u),
                   static_cast<uint8_t>((v >> 25) & 1u)};
 }
+
+struct SplitOperand {
+  int64_t lines, line_stride, k_stride, plane, ld;  // strides of X in doubles, ld in bytes
+  const double* X;
+  const int32_t* E;
+  int8_t* D;
+  int tiles, blocks, panels, unused;  // tiles: blocks of threads along the lines
+};
+struct SplitArgs {
+  SplitOperand op[2];  // A, B
+  int64_t K, kp;
+  int L, gbits;
+  uint32_t b[2][kModMaxBlocks];
+};
 
 // 32 bits of the integer I starting at bit `lo` (uniform), by unrolled selects.
 template <int NW>
@@ -61,20 +76,46 @@ __device__ inline uint32_t pack4(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
   return ab | (cd << 16);
 }
 
-// The residue panels of one block with at most ND dwords of bits.
-template <int NW, int ND>
-__device__ inline void residue_panels(const uint64_t (&I)[4][NW], const float (&sgn)[4], ModBlock blk,
+// The integers of a thread's four elements: 32 bits of each from bit `lo` on.
+template <int NW>
+struct RegisterWords {
+  uint64_t I[4][NW];
+  __device__ inline void get(int lo, uint32_t (&v)[4]) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = bits_at<NW>(I[i], lo);
+  }
+};
+// Long integers wait in LDS, [dword][thread] with the four elements side by side,
+// instead of unrolled selects over up to 15 words.
+struct LdsWords {
+  const uint4* w;
+  int threads;
+  __device__ inline void get(int lo, uint32_t (&v)[4]) const {
+    const int wi = lo >> 5, b = lo & 31;
+    const uint4 x = w[wi * threads], y = w[(wi + 1) * threads];
+    v[0] = __builtin_amdgcn_alignbit(y.x, x.x, b);
+    v[1] = __builtin_amdgcn_alignbit(y.y, x.y, b);
+    v[2] = __builtin_amdgcn_alignbit(y.z, x.z, b);
+    v[3] = __builtin_amdgcn_alignbit(y.w, x.w, b);
+  }
+};
+
+// The residue panels c0 .. c1 - 1 of one block with at most ND dwords of bits.
+template <int ND, class Words>
+__device__ inline void residue_panels(const Words& words, const float (&sgn)[4], ModBlock blk, int c0, int c1,
                                       int8_t* __restrict__ out, int64_t kp, bool store) {
   uint32_t e[4][ND];
 #pragma unroll
   for (int j = 0; j < ND; ++j) {
     const int left = blk.bits - 32 * j;  // uniform
     const uint32_t mask = left >= 32 ? 0xffffffffu : (left > 0 ? (1u << left) - 1u : 0u);
+    uint32_t v[4] = {0, 0, 0, 0};
+    if (left > 0) words.get(blk.lo + 32 * j, v);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) e[i][j] = left > 0 ? bits_at<NW>(I[i], blk.lo + 32 * j) & mask : 0u;
+    for (int i = 0; i < 4; ++i) e[i][j] = v[i] & mask;
   }
   const int row = blk.scaled ? mod_row(blk.count, 0) : kModRows;
-  for (int c = 0; c < blk.count; ++c) {
+  for (int c = c0; c < c1; ++c) {
     const uint32_t* t = kResidueTable.row[row + c];
     uint32_t k[ND];
 #pragma unroll
@@ -97,13 +138,15 @@ __device__ inline void residue_panels(const uint64_t (&I)[4][NW], const float (&
 
 // The sub-digit panels of one digit: the C balanced sub-digits, then the sums of
 // every two of them (each in [-128, 127]); one sub-digit is the digit itself.
-template <int NW, int C>
-__device__ inline void direct_panels(const uint64_t (&I)[4][NW], const float (&sgn)[4], ModBlock blk,
+template <int C, class Words>
+__device__ inline void direct_panels(const Words& words, const float (&sgn)[4], ModBlock blk,
                                      int8_t* __restrict__ out, int64_t kp, bool store) {
   int32_t s[4][C];
+  uint32_t f[4];
+  words.get(blk.lo, f);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int32_t d = static_cast<int32_t>(bits_at<NW>(I[i], blk.lo) & ((1u << blk.bits) - 1u));
+    const int32_t d = static_cast<int32_t>(f[i] & ((1u << blk.bits) - 1u));
     int32_t v = sgn[i] < 0.0f ? -d : d;
 #pragma unroll
     for (int j = 0; j + 1 < C; ++j) {
@@ -129,42 +172,61 @@ __device__ inline void direct_panels(const uint64_t (&I)[4][NW], const float (&s
       put(s[0][j] + s[0][l], s[1][j] + s[1][l], s[2][j] + s[2][l], s[3][j] + s[3][l]);
 }
 
+// The panels p0 .. p1 - 1 of the operand, all its blocks in turn.
+template <class Words>
+__device__ inline void all_panels(const Words& words, const float (&sgn)[4], const uint32_t* __restrict__ blocks,
+                                  int count, int p0, int p1, int8_t* __restrict__ out, int64_t kp, bool store) {
+  int first = 0;
+  for (int b = 0; b < count; ++b) {
+    const ModBlock blk = unpack_block(blocks[b]);
+    if (blk.residue) {
+      const int c0 = p0 > first ? p0 - first : 0, c1 = p1 - first < blk.count ? p1 - first : blk.count;
+      if (c0 < c1) {
+        if (blk.bits <= 32) residue_panels<1>(words, sgn, blk, c0, c1, out, kp, store);
+        else if (blk.bits <= 64) residue_panels<2>(words, sgn, blk, c0, c1, out, kp, store);
+        else if (blk.bits <= 128) residue_panels<4>(words, sgn, blk, c0, c1, out, kp, store);
+        else residue_panels<6>(words, sgn, blk, c0, c1, out, kp, store);
+      }
+    } else if (first >= p0 && first < p1) {  // a digit's panels go together
+      if (blk.count == 1) direct_panels<1>(words, sgn, blk, out, kp, store);
+      else if (blk.count == 3) direct_panels<2>(words, sgn, blk, out, kp, store);
+      else if (blk.count == 6) direct_panels<3>(words, sgn, blk, out, kp, store);
+      else direct_panels<4>(words, sgn, blk, out, kp, store);
+    }
+    out += static_cast<int64_t>(blk.count) * kp;
+    first += blk.count;
+  }
+}
+
 // kWin: 2 or 4, the 128- or 256-bit integer floor; 0, the general one.
 template <int NW, int ML, int TK, int kWin>
-__global__ void __launch_bounds__(4 * TK) modular_split_kernel(int64_t lines, int64_t K, int64_t line_stride,
-                                                               int64_t k_stride, int64_t plane, int64_t kp,
-                                                               int64_t ld, int L, int gbits,
-                                                               const double* __restrict__ X,
-                                                               const int32_t* __restrict__ E,
-                                                               int8_t* __restrict__ D, SplitBlocks blocks) {
+__global__ void __launch_bounds__(4 * TK) modular_split_kernel(SplitArgs) {
   constexpr int kPitch = TK + 2;
   extern __shared__ double tile[];  // [L][kLines][kPitch]
-  const int t = threadIdx.x;
-  const int64_t c0 = static_cast<int64_t>(blockIdx.x) * kLines;
-  const int64_t k0 = static_cast<int64_t>(blockIdx.y) * TK;
+  // the argument in place (see modular_accum.hip)
+  const SplitArgs& args = *(const SplitArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  const int which = static_cast<int>(blockIdx.x) < args.op[0].tiles ? 0 : 1;
+  const SplitOperand& op = args.op[which];
+  const int L = args.L, t = threadIdx.x;
+  const int64_t c0 = static_cast<int64_t>(blockIdx.x - (which ? args.op[0].tiles : 0)) * kLines;
+  const int64_t k0 = static_cast<int64_t>(blockIdx.y) * TK, K = args.K, kp = args.kp, lines = op.lines;
   // the tile's limbs, 4 elements per thread (+0.0 outside the operand)
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int x = t + i * 4 * TK;
-    int line, kk;
-    if (k_stride == 1) {
-      line = x / TK;
-      kk = x % TK;
-    } else {
-      line = x % kLines;
-      kk = x / kLines;
-    }
+    const bool rows = op.k_stride == 1;
+    const int line = rows ? x / TK : x % kLines, kk = rows ? x % TK : x / kLines;
     const bool ok = c0 + line < lines && k0 + kk < K;
-    const int64_t idx = ok ? (c0 + line) * line_stride + (k0 + kk) * k_stride : 0;
+    const int64_t idx = ok ? (c0 + line) * op.line_stride + (k0 + kk) * op.k_stride : 0;
     for (int l = 0; l < L; ++l)
-      tile[(l * kLines + line) * kPitch + kk] = ok ? X[static_cast<int64_t>(l) * plane + idx] : 0.0;
+      tile[(l * kLines + line) * kPitch + kk] = ok ? op.X[static_cast<int64_t>(l) * op.plane + idx] : 0.0;
   }
   __syncthreads();
   const int line = t / (TK / 4), kq = 4 * (t % (TK / 4));
   const int64_t c = c0 + line, kk = k0 + kq;
   const bool store = c < lines && kk < kp;
-  const int g = (c < lines ? E[c] : 0) - gbits;  // the grid exponent E - w S
-  uint64_t I[4][NW];
+  const int g = (c < lines ? op.E[c] : 0) - args.gbits;  // the grid exponent E - w S
+  RegisterWords<NW> words;
   float sgn[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -173,73 +235,81 @@ __global__ void __launch_bounds__(4 * TK) modular_split_kernel(int64_t lines, in
     for (int l = 0; l < ML; ++l) xs[l] = l < L ? tile[(l * kLines + line) * kPitch + kq + i] : 0.0;
     bool neg;
     if constexpr (kWin == 2)
-      neg = floor_on_grid_128<ML>(xs, L, g, I[i]);
+      neg = floor_on_grid_128<ML>(xs, L, g, words.I[i]);
     else if constexpr (kWin == 4)
-      neg = floor_on_grid_256<ML>(xs, L, g, I[i]);
+      neg = floor_on_grid_256<ML>(xs, L, g, words.I[i]);
     else
-      neg = floor_on_grid<NW, ML>(xs, L, g, I[i]);
+      neg = floor_on_grid<NW, ML>(xs, L, g, words.I[i]);
     sgn[i] = neg ? -1.0f : 1.0f;
   }
-  int8_t* out = D + c * ld + kk;
-  for (int b = 0; b < blocks.count; ++b) {
-    const ModBlock blk = unpack_block(blocks.b[b]);
-    if (blk.residue) {
-      if (blk.bits <= 32) residue_panels<NW, 1>(I, sgn, blk, out, kp, store);
-      else if (blk.bits <= 64) residue_panels<NW, 2>(I, sgn, blk, out, kp, store);
-      else if (blk.bits <= 128) residue_panels<NW, 4>(I, sgn, blk, out, kp, store);
-      else residue_panels<NW, 6>(I, sgn, blk, out, kp, store);
-    } else if (blk.count == 1) {
-      direct_panels<NW, 1>(I, sgn, blk, out, kp, store);
-    } else if (blk.count == 3) {
-      direct_panels<NW, 2>(I, sgn, blk, out, kp, store);
-    } else if (blk.count == 6) {
-      direct_panels<NW, 3>(I, sgn, blk, out, kp, store);
-    } else {
-      direct_panels<NW, 4>(I, sgn, blk, out, kp, store);
+  int8_t* out = op.D + c * op.ld + kk;
+  const int z = blockIdx.z, nz = gridDim.z;
+  const int p0 = op.panels * z / nz, p1 = op.panels * (z + 1) / nz;
+  if constexpr (NW >= 8) {
+    __syncthreads();  // the tile's readers are done
+    uint4* w = reinterpret_cast<uint4*>(tile) + t;
+#pragma unroll
+    for (int i = 0; i < 2 * NW + 1; ++i) {
+      auto at = [&](int e) {
+        return i < 2 * NW ? static_cast<uint32_t>(words.I[e][i / 2 < NW ? i / 2 : 0] >> (32 * (i & 1))) : 0u;
+      };
+      w[i * 4 * TK] = make_uint4(at(0), at(1), at(2), at(3));
     }
-    out += static_cast<int64_t>(blk.count) * kp;
+    // every thread reads its own words only
+    all_panels(LdsWords{w, 4 * TK}, sgn, args.b[which], op.blocks, p0, p1, out, kp, store);
+  } else {
+    all_panels(words, sgn, args.b[which], op.blocks, p0, p1, out, kp, store);
   }
 }
 
 template <int NW, int ML, int TK, int kWin>
-hipError_t launch_split_tile(int64_t lines, int64_t K, int64_t ls, int64_t ks, int64_t plane, int64_t kp, int L,
-                             int gbits, const double* X, const int32_t* E, int8_t* D,
-                             const std::vector<ModBlock>& blocks, int panels, hipStream_t stream) {
-  if (blocks.size() > static_cast<size_t>(kModMaxBlocks) || panels > kModMaxPanels) return hipErrorInvalidValue;
-  SplitBlocks sb;
-  sb.count = static_cast<int>(blocks.size());
-  std::transform(blocks.begin(), blocks.end(), sb.b, pack_block);
-  const size_t lds = sizeof(double) * static_cast<size_t>(L) * kLines * (TK + 2);
-  const int64_t gx = (lines + kLines - 1) / kLines, gy = (kp + TK - 1) / TK;
+hipError_t launch_split_tile(SplitArgs& a, hipStream_t stream) {
+  size_t lds = sizeof(double) * static_cast<size_t>(a.L) * kLines * (TK + 2);
+  if (NW >= 8) lds = std::max(lds, sizeof(uint4) * (2 * NW + 1) * 4 * TK);
+  int64_t gx = 0;
+  for (SplitOperand& op : a.op) {
+    const int64_t tiles = (op.lines + kLines - 1) / kLines;
+    if (tiles > (1 << 30)) return hipErrorInvalidValue;
+    op.tiles = static_cast<int>(tiles);
+    gx += tiles;
+  }
+  const int64_t gy = (a.kp + TK - 1) / TK;
   if (gy > 65535 || gx > 0x7fffffff) return hipErrorInvalidValue;
+  const int64_t gz = std::min<int64_t>(8, std::max<int64_t>(1, 512 / (gx * gy)));
   auto kernel = modular_split_kernel<NW, ML, TK, kWin>;
   if (lds > 64 * 1024) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(gx), static_cast<unsigned>(gy)), dim3(4 * TK), lds, stream,
-                     lines, K, ls, ks, plane, kp, static_cast<int64_t>(panels) * kp, L, gbits, X, E, D, sb);
+  hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(gx), static_cast<unsigned>(gy), static_cast<unsigned>(gz)),
+                     dim3(4 * TK), lds, stream, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_modular_split(int64_t rows, int64_t cols, int L, int S, int w, int axis, const double* X,
-                                const int32_t* E, int8_t* D, const ModPlan& pl, hipStream_t stream) {
-  const int64_t lines = axis == 0 ? rows : cols, K = axis == 0 ? cols : rows;
-  if (lines == 0 || K == 0) return hipSuccess;
-  const int64_t ls = axis == 0 ? cols : 1, ks = axis == 0 ? 1 : cols, plane = rows * cols, kp = mod_kp(K);
-  const std::vector<ModBlock>& blocks = axis == 0 ? pl.a : pl.b;
-  const int panels = axis == 0 ? pl.pa : pl.pb, bits = w * S, words = (bits + 52 + 63) / 64;
-#define MDG_MOD_SPLIT(NW, ML, TK, WIN) \
-  launch_split_tile<NW, ML, TK, WIN>(lines, K, ls, ks, plane, kp, L, bits, X, E, D, blocks, panels, stream)
-  if (L <= 2 && bits <= 128) return MDG_MOD_SPLIT(2, 2, 128, 2);
-  if (L <= 4 && bits <= 256) return MDG_MOD_SPLIT(4, 4, 128, 4);
-  if (L <= 4 && words <= 8) return MDG_MOD_SPLIT(8, 4, 128, 0);
-  if (L <= 8 && words <= 8) return MDG_MOD_SPLIT(8, 8, 64, 0);
-  if (words <= 15) return MDG_MOD_SPLIT(15, 16, 64, 0);
-#undef MDG_MOD_SPLIT
+hipError_t launch_modular_split(int64_t m, int64_t n, int64_t k, int L, int S, int w, const double* A,
+                                const double* B, const int32_t* EA, const int32_t* EB, int8_t* DA, int8_t* DB,
+                                const ModPlan& pl, hipStream_t stream) {
+  if (m == 0 || n == 0 || k == 0) return hipSuccess;
+  if (pl.a.size() > static_cast<size_t>(kModMaxBlocks) || pl.b.size() > static_cast<size_t>(kModMaxBlocks))
+    return hipErrorInvalidValue;
+  SplitArgs a{};
+  a.K = k;
+  a.kp = mod_kp(k);
+  a.L = L;
+  a.gbits = w * S;
+  a.op[0] = SplitOperand{m, k, 1, m * k, pl.pa * a.kp, A, EA, DA, 0, static_cast<int>(pl.a.size()), pl.pa, 0};
+  a.op[1] = SplitOperand{n, 1, n, k * n, pl.pb * a.kp, B, EB, DB, 0, static_cast<int>(pl.b.size()), pl.pb, 0};
+  std::transform(pl.a.begin(), pl.a.end(), a.b[0], pack_block);
+  std::transform(pl.b.begin(), pl.b.end(), a.b[1], pack_block);
+  const int bits = w * S, words = (bits + 52 + 63) / 64;
+  if (L <= 2 && bits <= 128) return launch_split_tile<2, 2, 128, 2>(a, stream);
+  if (L <= 4 && bits <= 256) return launch_split_tile<4, 4, 128, 4>(a, stream);
+  if (L <= 4 && words <= 8) return launch_split_tile<8, 4, 64, 0>(a, stream);
+  if (L <= 8 && words <= 8) return launch_split_tile<8, 8, 64, 0>(a, stream);
+  if (words <= 15) return launch_split_tile<15, 16, 64, 0>(a, stream);
   return hipErrorInvalidValue;
 }
 
