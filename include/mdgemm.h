@@ -199,14 +199,18 @@ typedef struct mdgemm_opts {
  * with one int8 product per modulus and recovered by the Chinese remainder theorem,
  * or, for single pairs, by Karatsuba's identity on 7-bit sub-digits: every limb
  * equals that of the FP64 level products.  Not with MDGEMM_STAGED, MDGEMM_INT8,
- * MDGEMM_KARATSUBA_MIN_TERMS or the grouped products, nor for k above 2^15. */
+ * MDGEMM_KARATSUBA_MIN_TERMS or the grouped products, nor for k above 2^15.
+ * In a workspace that may be read, the pair schedule's levels are formed one by one
+ * on the int8 matrix cores over 7-bit sub-digits where that is estimated faster; the
+ * workspace then holds the same exponents, digits and levels. */
 
 /* Logging.  With the environment variable MDGEMM_LOG=1 (read once per process)
  * every call of mdgemm, mdgemm_ex, mdgemm_ex_noalloc and mdgemm_qr_dd writes one
  * line to stderr when it returns: its sizes, the plan (w, S, T; "unplanned" for
  * arguments that do not resolve), the flags, the workspace kind, the stream, the
  * path taken (refused, empty, zero (k = 0), fused small product, int8 residues,
- * staged: pair levels / karatsuba / grouped products, int8 levels) and the status string.
+ * int8 sub-digits: pair levels, staged: pair levels / karatsuba / grouped products,
+ * int8 levels) and the status string.
  * MDGEMM_LOG=2 also logs the products a QR makes.  Unset or 0: silent. */
 
 /* Fill `opts` with the defaults: default stream, library workspace, the default

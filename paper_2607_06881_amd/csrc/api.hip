@@ -586,6 +586,33 @@ bool layout(int64_t m, int64_t n, int64_t k, const Planned& pl, int w, Layout* L
   return true;
 }
 
+// A caller workspace that may be read afterwards holds the levels and the digit
+// panels of the pair schedule: its levels are formed on the int8 matrix cores over
+// 7-bit sub-digits (LevelPlan; every level the same integer as the FP64 GEMM's), with
+// the int8 panels in the digit panels' place until the digits are written there last,
+// where that is estimated faster than the FP64 level GEMM.  The estimate: c^2 products
+// per pair at the int8 rate, on 256 x 256 tiles, the heaviest level at least, and
+// 2c - 1 passes over every level plane.
+bool levels_on_int8(int64_t m, int64_t n, int64_t k, const Resolved& r, const Planned& pl, const Layout& L) {
+  if (r.kind != Kind::kLevels || !pl.s.direct_levels || (r.flags & (MDGEMM_STAGED | MDGEMM_INT8)) || r.Ge > 1 ||
+      r.sign)
+    return false;
+  const int c = mdg::sub_digits(r.w), heaviest = max_pairs(r.S, r.T), pairs = pair_count(r.S, r.T);
+  const int64_t kp = mdg::mod_kp(k), panels = int64_t{c} * r.S;
+  if (n > mdg::kLevelsMaxN || c * r.S > mdg::kModMaxBlocks || !mdg::modular_gemm_fits(kp, static_cast<int>(panels))) return false;
+  // int32 sums of products of magnitude 2^12
+  if (static_cast<double>(heaviest) * c * static_cast<double>(k) >= static_cast<double>(1 << 19)) return false;
+  if (static_cast<size_t>(kp * panels) * static_cast<size_t>(mdg::mod_rows(m)) > L.db - L.da ||
+      static_cast<size_t>(kp * panels) * static_cast<size_t>(mdg::mod_rows(n)) > L.g - L.db)
+    return false;
+  const double tile = 2.0 * 65536.0 * static_cast<double>(kp) * c * c / (2.2e15 / 256);  // one pair of one tile on a CU
+  const double tiles = static_cast<double>(mdg::mod_rows(m)) * static_cast<double>(mdg::mod_rows(n)) / 65536.0;
+  const double passes = (2 * c - 1) * 8e-6;
+  const double us = 1e6 * (std::max(heaviest * tile + passes,
+                                    (pairs * tile + (r.T + 1) * passes) * tiles / 256)) + 70.0;
+  return us < staged_estimate_us(m, n, k, r.T, heaviest, pairs);
+}
+
 // The level sums of a resolved product stay exact: below 2^53 on the FP64
 // matrix cores, below 2^31 on the int8 ones.
 bool resolved_exact(const Resolved& r, int64_t k) {
@@ -887,7 +914,8 @@ int enqueue_modular(int64_t m, int64_t n, int64_t k, int limbs, const double* A,
   // the partial column maxima go through the planes' region, written later
   MDG_TRY(hip_status(mdg::launch_exponents_ab(m, k, n, A, B, EA, EB, P, L.total - L.p, s)));
   if (timed) MDG_TRY(record(1, s));
-  MDG_TRY(hip_status(mdg::launch_modular_split(m, n, k, limbs, r.S, r.w, A, B, EA, EB, DA, DB, pl, s)));
+  MDG_TRY(hip_status(mdg::launch_modular_split(m, n, k, limbs, r.S, r.w, A, B, EA, EB, DA, DB, pl.a, pl.pa, pl.b,
+                                               pl.pb, s)));
   if (timed) MDG_TRY(record(2, s));
   MDG_TRY(hip_status(mdg::launch_modular_gemm(m, n, mdg::mod_kp(k), pl, DA, DB, P, s)));
   if (timed) MDG_TRY(record(3, s));
@@ -1083,6 +1111,8 @@ int ex_impl(int64_t m, int64_t n, int64_t k, int limbs, const double* A, const d
     MDG_TRY(lib.acquire(L.total, s, &ws));
   }
   const Parts w = parts(ws, L);
+  const bool int8_levels = caller_ws && levels_on_int8(m, n, k, r, *pl, L);
+  if (int8_levels) *path = "int8 sub-digits: pair levels";
 
   auto enqueue = [&]() -> int {
     if (r.flags & MDGEMM_CHECK_FINITE) MDG_TRY(check_finite(m, n, k, limbs, A, B, w.flag, s));
@@ -1099,6 +1129,25 @@ int ex_impl(int64_t m, int64_t n, int64_t k, int limbs, const double* A, const d
     // a2: exact splits into S digit panels and, beside them, the schedule's
     // combinations (digit sums) from the same integers
     MDG_TRY(hip_status(mdg::launch_upload(pl->t.words, w.table, s)));
+    if (int8_levels) {
+      const mdg::LevelPlan lp = mdg::level_plan(r.S, r.T, r.w);
+      int8_t *da = static_cast<int8_t*>(w.DA), *db = static_cast<int8_t*>(w.DB);
+      const int panels = lp.c * lp.S;
+      MDG_TRY(hip_status(mdg::launch_modular_split(m, n, k, limbs, r.S, r.w, A, B, w.EA, w.EB, da, db, lp.a, panels,
+                                                   lp.b, panels, s)));
+      if (timed) MDG_TRY(record(2, s));
+      MDG_TRY(hip_status(mdg::launch_modular_levels(m, n, mdg::mod_kp(k), lp, da, db, w.G, s)));
+      if (timed) MDG_TRY(record(3, s));
+      MDG_TRY(hip_status(mdg::launch_accum_renorm(m, n, limbs, r.T + 1, r.w, w.G, w.EA, w.EB, C, s)));
+      // the digits that the workspace holds after the call
+      MDG_TRY(hip_status(mdg::launch_split(m, k, limbs, r.S, r.w, 0, A, w.EA, w.DA, true, s, nullptr, 0, w.f32)));
+      MDG_TRY(hip_status(mdg::launch_split(k, n, limbs, r.S, r.w, 1, B, w.EB, w.DB, true, s, nullptr, 0, w.f32)));
+      if (timed) {
+        MDG_TRY(record(4, s));
+        timing().valid = true;
+      }
+      return MDGEMM_OK;
+    }
     if (r.kind == Kind::kGroups) {
       // grouped digits: each element's S digits in its group's panels, on its class grid
       MDG_TRY(hip_status(mdg::launch_split_groups(m, k, limbs, r.S, r.w, 0, A, w.EA, w.DA, w.f32, r.Ge, r.sign, s)));

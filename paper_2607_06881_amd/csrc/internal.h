@@ -118,16 +118,20 @@ bool level_gemm_i8_fits(int64_t kp, int S);
 hipError_t launch_level_gemm_i8(int64_t m, int64_t n, int64_t kp, int S, int T, const int8_t* DA, const int8_t* DBt,
                                 int32_t* G, hipStream_t stream);
 
-// The int8 products of a plan (modular.h): a2, the panels of A (rows of pl.pa
-// panels) and of B (columns of pl.pb), mod_kp(k) bytes each, mod_rows() rows of
-// memory; a3, the output planes P (4 pl.planes mod_quads(m) n bytes, 16-byte
+// The int8 products of a plan (modular.h): a2, the panels of A (rows of pa panels
+// made of the blocks ba) and of B (columns of pb, of bb), mod_kp(k) bytes each,
+// mod_rows() rows of memory; a3, the output planes P (4 pl.planes mod_quads(m) n bytes, 16-byte
 // aligned); a4 + a5 from the planes.
 hipError_t launch_modular_split(int64_t m, int64_t n, int64_t k, int L, int S, int w, const double* A,
                                 const double* B, const int32_t* EA, const int32_t* EB, int8_t* DA, int8_t* DB,
-                                const ModPlan& pl, hipStream_t stream);
+                                const std::vector<ModBlock>& ba, int pa, const std::vector<ModBlock>& bb, int pb,
+                                hipStream_t stream);
 bool modular_gemm_fits(int64_t kp, int panels);
 hipError_t launch_modular_gemm(int64_t m, int64_t n, int64_t kp, const ModPlan& pl, const int8_t* DA, const int8_t* DB,
                                uint32_t* P, hipStream_t stream);
+// The levels of a LevelPlan as integer-valued doubles G [T+1][m][n].
+hipError_t launch_modular_levels(int64_t m, int64_t n, int64_t kp, const LevelPlan& lp, const int8_t* DA,
+                                 const int8_t* DB, double* G, hipStream_t stream);
 hipError_t launch_modular_accum(int64_t m, int64_t n, int L, int T, int w, const ModPlan& pl, const uint32_t* P,
                                 const int32_t* EA, const int32_t* EB, double* C, hipStream_t stream);
 

@@ -47,10 +47,11 @@ constexpr int kModuli[kMaxModuli] = {256, 255, 253, 251, 247, 241, 239, 233, 229
 // Digits p0 .. p0 + u - 1 of an operand as one integer: bits lo .. lo + bits - 1
 // of D; `count` int8 panels are made from it: residues modulo the first `count`
 // moduli (residue, with the factors of the `count`-moduli system folded in when
-// scaled), or the sub-digit types of one digit (direct).
+// scaled), or the sub-digit types of one digit (direct), or sub-digit pick - 1 of
+// one digit alone (scaled marks the top one).
 struct ModBlock {
   uint16_t lo;
-  uint8_t bits, count, residue, scaled;
+  uint8_t bits, count, residue, scaled, pick;
 };
 
 // One int8 product: panels a + i da of A times b + i db of B, i < nseg, summed;
@@ -80,6 +81,21 @@ struct ModPlan {
   int64_t products = 0;  // int8 products of length k
   double seconds = 0.0;  // estimated time, for choosing the path
 };
+
+// Levels in place: where the level planes G_t themselves are wanted (a caller
+// workspace that may be read), each level is formed by one job over sub-digits of 7
+// bits: with c of them, pass s = 0 .. 2c - 2 sums the products of sub-digits i + j = s
+// of the level's pairs in int32 and adds 2^(7 s) times that to the level.  Panels:
+// sub-digit i of digit p of A at i S + p, sub-digit j of digit q of B at j S + S - 1 - q,
+// so that a level's pairs are one contiguous run for each (i, j).
+struct LevelPlan {
+  std::vector<ModBlock> a, b;
+  int S = 0, T = 0, c = 0;
+};
+LevelPlan level_plan(int S, int T, int w);
+constexpr int64_t kLevelsMaxN = int64_t{1} << 20;  // a tile's rows of a plane in 32-bit offsets
+// 7-bit sub-digits of a w-bit digit (balanced, the last one up to 64 in magnitude).
+inline int sub_digits(int w) { return w <= 7 ? 1 : (w + 7) / 7; }
 
 // The plan for the digit pairs p + q <= T of S digits of w bits and an m x k by
 // k x n product; nullptr when none fits the limits above (or the int32 sums).

@@ -164,14 +164,15 @@ __device__ __forceinline__ void tile_loop(int8_t* __restrict__ P0, int8_t* __res
   __builtin_amdgcn_s_waitcnt(kWaitVmLgkm0);
 }
 
-__global__ void __launch_bounds__(512, 1) modular_gemm_kernel(int64_t m, int64_t n, int64_t kp, int64_t lda,
-                                                              int64_t ldb, int tiles_n, int ntiles, int group,
-                                                              const int8_t* __restrict__ DA,
-                                                              const int8_t* __restrict__ DB,
-                                                              uint32_t* __restrict__ P, Jobs jobs) {
-  __shared__ __attribute__((aligned(1024))) int8_t P0[kBuf];
-  __shared__ __attribute__((aligned(1024))) int8_t P1[kBuf];
-
+// Where a block's tile and a lane's fragments and copies lie.
+struct Tile {
+  int64_t m0, n0;
+  uint32_t la0, la1, lb0, lb1;  // copies: byte offsets of this lane from the tile's first row
+  int fa0, fa1, fb0, fb1;       // fragments: LDS offsets
+  int lane, wave, wr, wc;
+};
+__device__ __forceinline__ Tile tile_of(int64_t lda, int64_t ldb, int tiles_n, int ntiles, int group) {
+  Tile t;
   // tile order: block b runs on XCD b % 8; XCD x takes the chunk [x per, (x+1) per)
   // of an order that walks patches of `group` tile-rows column by column
   int tt = blockIdx.x;
@@ -182,8 +183,49 @@ __global__ void __launch_bounds__(512, 1) modular_gemm_kernel(int64_t m, int64_t
   const int tiles_m = ntiles / tiles_n;
   const int gsz = group * tiles_n, g = tt / gsz, first = g * group;
   const int rows_in = min(group, tiles_m - first), within = tt - g * gsz;
-  const int64_t m0 = static_cast<int64_t>(first + within % rows_in) * kTile;
-  const int64_t n0 = static_cast<int64_t>(within / rows_in) * kTile;
+  t.m0 = static_cast<int64_t>(first + within % rows_in) * kTile;
+  t.n0 = static_cast<int64_t>(within / rows_in) * kTile;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  t.lane = lane;
+  t.wave = wave;
+  t.wr = wave >> 2;
+  t.wc = wave & 3;
+  // copies: lane L of instruction q lands at tile row 32 wave + 8q + L/8 (= 8 (q&1) + L/8
+  // mod 16), granule L%8, and fetches logical granule (L%8) ^ swz(row) of that row
+  const int lr = 32 * wave + (lane >> 3);
+  const uint32_t g0 = static_cast<uint32_t>(((lane & 7) ^ swz(lane >> 3)) << 4);
+  const uint32_t g1 = static_cast<uint32_t>(((lane & 7) ^ swz(8 + (lane >> 3))) << 4);
+  const uint32_t ra = static_cast<uint32_t>(lr * lda), rb = static_cast<uint32_t>(lr * ldb);
+  t.la0 = ra + g0;
+  t.la1 = ra + g1;
+  t.lb0 = rb + g0;
+  t.lb1 = rb + g1;
+  // fragments: lane l reads row 16 i + l%16 of the wave's 128 rows of A (64 columns of B),
+  // logical granule 4h + l/16
+  const int l = lane & 15;
+  const int s0 = (((lane >> 4) ^ swz(l)) << 4) + l * kStage, s1 = (((4 + (lane >> 4)) ^ swz(l)) << 4) + l * kStage;
+  t.fa0 = t.wr * 128 * kStage + s0;
+  t.fa1 = t.wr * 128 * kStage + s1;
+  t.fb0 = t.wc * 64 * kStage + s0;
+  t.fb1 = t.wc * 64 * kStage + s1;
+  return t;
+}
+
+__device__ __forceinline__ void clear(v4i (&acc)[8][4]) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = v4i{0, 0, 0, 0};
+}
+
+__global__ void __launch_bounds__(512, 1) modular_gemm_kernel(int64_t m, int64_t n, int64_t kp, int64_t lda,
+                                                              int64_t ldb, int tiles_n, int ntiles, int group,
+                                                              const int8_t* __restrict__ DA,
+                                                              const int8_t* __restrict__ DB,
+                                                              uint32_t* __restrict__ P, Jobs jobs) {
+  __shared__ __attribute__((aligned(1024))) int8_t P0[kBuf];
+  __shared__ __attribute__((aligned(1024))) int8_t P1[kBuf];
+  const Tile t = tile_of(lda, ldb, tiles_n, ntiles, group);
   ModJob job;
   {
     const uint32_t w0 = jobs.j[blockIdx.y][0], w1 = jobs.j[blockIdx.y][1], w2 = jobs.j[blockIdx.y][2];
@@ -204,35 +246,14 @@ __global__ void __launch_bounds__(512, 1) modular_gemm_kernel(int64_t m, int64_t
   walk.within = 0;
   walk.spk = spk;
 
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wr = wave >> 2, wc = wave & 3;
-  // copies: lane L of instruction q lands at tile row 32 wave + 8q + L/8 (= 8 (q&1) + L/8
-  // mod 16), granule L%8, and fetches logical granule (L%8) ^ swz(row) of that row
-  const int lr = 32 * wave + (lane >> 3);
-  const uint32_t g0 = static_cast<uint32_t>(((lane & 7) ^ swz(lane >> 3)) << 4);
-  const uint32_t g1 = static_cast<uint32_t>(((lane & 7) ^ swz(8 + (lane >> 3))) << 4);
-  const uint32_t ra = static_cast<uint32_t>(lr * lda), rb = static_cast<uint32_t>(lr * ldb);
-  // fragments: lane l reads row 16 i + l%16 of the wave's 128 rows of A (64 columns of B),
-  // logical granule 4h + l/16
-  int fa[2], fb[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int l = lane & 15, gl = 4 * h + (lane >> 4);
-    const int sw = ((gl ^ swz(l)) << 4) + l * kStage;
-    fa[h] = wr * 128 * kStage + sw;
-    fb[h] = wc * 64 * kStage + sw;
-  }
   v4i acc[8][4];
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = v4i{0, 0, 0, 0};
-  tile_loop(P0, P1, DA + m0 * lda, DB + n0 * ldb, static_cast<uint32_t>(kTile * lda),
+  clear(acc);
+  tile_loop(P0, P1, DA + t.m0 * lda, DB + t.n0 * ldb, static_cast<uint32_t>(kTile * lda),
             static_cast<uint32_t>(kTile * ldb), nst, walk, static_cast<uint32_t>(8 * lda),
-            static_cast<uint32_t>(8 * ldb), ra + g0, ra + g1, rb + g0, rb + g1, fa[0], fa[1], fb[0], fb[1], wave, acc);
+            static_cast<uint32_t>(8 * ldb), t.la0, t.la1, t.lb0, t.lb1, t.fa0, t.fa1, t.fb0, t.fb1, t.wave, acc);
 
   const int64_t quads = (m + 3) / 4, unit = quads * n;
-  const int64_t q0 = m0 / 4 + wr * 32 + (lane >> 4), j0 = n0 + wc * 64 + (lane & 15);
+  const int64_t q0 = t.m0 / 4 + t.wr * 32 + (t.lane >> 4), j0 = t.n0 + t.wc * 64 + (t.lane & 15);
   if (job.mod == kDirectJob) {
     v4i* o = reinterpret_cast<v4i*>(P + job.out * unit);
 #pragma unroll
@@ -267,7 +288,109 @@ __global__ void __launch_bounds__(512, 1) modular_gemm_kernel(int64_t m, int64_t
   }
 }
 
+constexpr uint32_t kOutside = 0xfffff000u;
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+
+// The levels of a LevelPlan: blockIdx.y is the position in `order` (heaviest level
+// first, a byte each).  Every pass reads the sums of the ones before it back from
+// the level's own plane (int64 until the last), which the same thread wrote.
+struct Levels {
+  int S, c;
+  uint32_t order[(kMaxLevels + 3) / 4];
+};
+__global__ void __launch_bounds__(512, 1) modular_levels_kernel(int64_t m, int64_t n, int64_t kp, int64_t ld,
+                                                                int tiles_n, int ntiles, int group,
+                                                                const int8_t* __restrict__ DA,
+                                                                const int8_t* __restrict__ DB, double* __restrict__ G,
+                                                                Levels levels) {
+  __shared__ __attribute__((aligned(1024))) int8_t P0[kBuf];
+  __shared__ __attribute__((aligned(1024))) int8_t P1[kBuf];
+  const Tile t = tile_of(ld, ld, tiles_n, ntiles, group);
+  const int level = (levels.order[blockIdx.y >> 2] >> (8 * (blockIdx.y & 3))) & 0xffu;
+  const int S = levels.S, c = levels.c;
+  const int p0 = level - (S - 1) > 0 ? level - (S - 1) : 0, p1 = level < S - 1 ? level : S - 1;
+  const int spk = static_cast<int>((p1 - p0 + 1) * kp / kStage);  // a run: the level's pairs for one (i, j)
+  // the tile's rows of the plane as a buffer, whose range check drops the rows beyond
+  // m; the columns beyond n get an offset outside of it
+  const uint32_t pitch = static_cast<uint32_t>(n * 8);
+  const __amdgpu_buffer_rsrc_t rg = __builtin_amdgcn_make_buffer_rsrc(
+      G + (static_cast<int64_t>(level) * m + t.m0) * n, 0,
+      static_cast<uint32_t>(m - t.m0 < kTile ? m - t.m0 : kTile) * pitch, kBufferWord3);
+  const int64_t j0 = t.n0 + t.wc * 64 + (t.lane & 15);
+  const uint32_t off0 = static_cast<uint32_t>(t.wr * 128 + 4 * (t.lane >> 4)) * pitch + static_cast<uint32_t>(j0 * 8);
+  const int cols = j0 >= n ? 0 : static_cast<int>((n - j0 + 15) / 16 < 4 ? (n - j0 + 15) / 16 : 4);  // of the lane's 4
+  for (int s = 0; s <= 2 * c - 2; ++s) {
+    const int i = s - (c - 1) > 0 ? s - (c - 1) : 0, runs = min(s, c - 1) - i + 1;
+    Walk walk;
+    walk.a = static_cast<uint32_t>((i * S + p0) * kp);
+    walk.b = static_cast<uint32_t>(((s - i) * S + S - 1 - level + p0) * kp);
+    walk.ja = static_cast<uint32_t>(static_cast<int32_t>(S * kp) - (spk - 1) * kStage);
+    walk.jb = static_cast<uint32_t>(-static_cast<int32_t>(S * kp) - (spk - 1) * kStage);
+    walk.within = 0;
+    walk.spk = spk;
+    v4i acc[8][4];
+    clear(acc);
+    tile_loop(P0, P1, DA + t.m0 * ld, DB + t.n0 * ld, static_cast<uint32_t>(kTile * ld),
+              static_cast<uint32_t>(kTile * ld), runs * spk, walk, static_cast<uint32_t>(8 * ld),
+              static_cast<uint32_t>(8 * ld), t.la0, t.la1, t.lb0, t.lb1, t.fa0, t.fa1, t.fb0, t.fb1, t.wave, acc);
+    const bool last = s == 2 * c - 2;
+    // 16 elements at a time: their loads are in flight together, and the offsets,
+    // formed anew in every pass, leave the accumulators their registers
+    uint32_t off = off0;
+    asm volatile("" : "+v"(off));
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      v2u old[4][4];
+      if (s > 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int y = 0; y < 4; ++y)
+            old[r][y] = __builtin_amdgcn_raw_buffer_load_b64(rg, y < cols ? off + r * pitch : kOutside, 128 * y, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+          int64_t v = static_cast<int64_t>(acc[x][y][r]) << (7 * s);
+          if (s > 0) v += static_cast<int64_t>(old[r][y][0] | static_cast<uint64_t>(old[r][y][1]) << 32);
+          if (last) v = __double_as_longlong(static_cast<double>(v));  // below 2^53: exact
+          const v2u d = {static_cast<uint32_t>(v), static_cast<uint32_t>(v >> 32)};
+          __builtin_amdgcn_raw_buffer_store_b64(d, rg, y < cols ? off + r * pitch : kOutside, 128 * y, 0);
+        }
+      off += 16 * pitch;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
 }  // namespace
+
+hipError_t launch_modular_levels(int64_t m, int64_t n, int64_t kp, const LevelPlan& lp, const int8_t* DA,
+                                 const int8_t* DB, double* G, hipStream_t stream) {
+  if (m == 0 || n == 0) return hipSuccess;
+  const int panels = lp.c * lp.S;
+  if (!modular_gemm_fits(kp, panels) || lp.T + 1 > kMaxLevels || n > kLevelsMaxN) return hipErrorInvalidValue;
+  const int64_t tiles_m = (m + kTile - 1) / kTile, tiles_n = (n + kTile - 1) / kTile;
+  const int64_t ntiles = tiles_m * tiles_n;
+  if (ntiles > 0x7fffffff) return hipErrorInvalidValue;
+  Levels lv{};
+  lv.S = lp.S;
+  lv.c = lp.c;
+  int at = 0;
+  for (int size = lp.S; size >= 1; --size)
+    for (int t = 0; t <= lp.T; ++t) {
+      const int lo = std::max(0, t - (lp.S - 1)), hi = std::min(t, lp.S - 1);
+      if (hi - lo + 1 != size) continue;
+      lv.order[at >> 2] |= static_cast<uint32_t>(t) << (8 * (at & 3));
+      ++at;
+    }
+  const int group = ntiles >= 1024 ? 2 : 4;
+  hipLaunchKernelGGL(modular_levels_kernel, dim3(static_cast<unsigned>(ntiles), static_cast<unsigned>(lp.T + 1)),
+                     dim3(512), 0, stream, m, n, kp, panels * kp, static_cast<int>(tiles_n),
+                     static_cast<int>(ntiles), group, DA, DB, G, lv);
+  return hipGetLastError();
+}
 
 bool modular_gemm_fits(int64_t kp, int panels) {
   return panels >= 1 && kp > 0 && kp % kStage == 0 && static_cast<int64_t>(kTile) * panels * kp < (int64_t{1} << 31);

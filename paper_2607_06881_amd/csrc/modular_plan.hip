@@ -112,8 +112,6 @@ class Coverer {
   std::vector<double> rect_;
 };
 
-int sub_digits(int w) { return w <= 7 ? 1 : (w + 7) / 7; }
-
 // The tables for one cover, at most `longest` rectangles per job; false when a limit
 // of the kernels does not hold.
 bool build(const std::vector<Rect>& rects, int64_t longest, int64_t k, int S, int T, int w, ModPlan* pl) {
@@ -141,9 +139,9 @@ bool build(const std::vector<Rect>& rects, int64_t longest, int64_t k, int S, in
   std::reverse(db.begin(), db.end());
   auto lo_of = [&](int p0, int u) { return w * (S - (p0 + u)); };
   for (int p : da) pl->a.push_back(ModBlock{static_cast<uint16_t>(lo_of(p, 1)), static_cast<uint8_t>(w),
-                                            static_cast<uint8_t>(types), 0, 0});
+                                            static_cast<uint8_t>(types), 0, 0, 0});
   for (int q : db) pl->b.push_back(ModBlock{static_cast<uint16_t>(lo_of(q, 1)), static_cast<uint8_t>(w),
-                                            static_cast<uint8_t>(types), 0, 0});
+                                            static_cast<uint8_t>(types), 0, 0, 0});
   pl->pa = static_cast<int>(da.size()) * types;
   pl->pb = static_cast<int>(db.size()) * types;
   pl->direct_bits = w;
@@ -154,7 +152,7 @@ bool build(const std::vector<Rect>& rects, int64_t longest, int64_t k, int S, in
     auto it = m->find(key);
     if (it != m->end()) return it->second;
     v->push_back(ModBlock{static_cast<uint16_t>(lo_of(p0, u)), static_cast<uint8_t>(w * u), static_cast<uint8_t>(nm),
-                          1, static_cast<uint8_t>(scaled)});
+                          1, static_cast<uint8_t>(scaled), 0});
     const int first = *np;
     *np += nm;
     (*m)[key] = first;
@@ -250,6 +248,26 @@ double estimate(const ModPlan& pl, int64_t m, int64_t n, int64_t k) {
 }
 
 }  // namespace
+
+LevelPlan level_plan(int S, int T, int w) {
+  LevelPlan lp;
+  lp.S = S;
+  lp.T = T;
+  lp.c = sub_digits(w);
+  for (int i = 0; i < lp.c; ++i)
+    for (int p = 0; p < S; ++p) {
+      ModBlock b{};
+      b.bits = static_cast<uint8_t>(w);
+      b.count = 1;
+      b.scaled = i == lp.c - 1;
+      b.pick = static_cast<uint8_t>(i + 1);
+      b.lo = static_cast<uint16_t>(w * (S - 1 - p));
+      lp.a.push_back(b);
+      b.lo = static_cast<uint16_t>(w * p);  // position p of B's run is digit S - 1 - p
+      lp.b.push_back(b);
+    }
+  return lp;
+}
 
 std::shared_ptr<const ModPlan> modular_plan(int64_t m, int64_t n, int64_t k, int S, int T, int w) {
   if (m < 1 || n < 1 || k < 1 || S < 1 || S > kMaxSlices || T < 0 || T > 2 * S - 2 || w < 1 || w > kMaxSliceBits ||

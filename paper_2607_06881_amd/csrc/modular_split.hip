@@ -39,12 +39,13 @@ __constant__ const ResidueTable kResidueTable = make_residue_table();
 // The blocks in one dword each (scalar loads need whole, aligned dwords).
 inline uint32_t pack_block(const ModBlock& b) {
   return b.lo | static_cast<uint32_t>(b.bits) << 10 | static_cast<uint32_t>(b.count) << 18 |
-         static_cast<uint32_t>(b.residue) << 24 | static_cast<uint32_t>(b.scaled) << 25;
+         static_cast<uint32_t>(b.residue) << 24 | static_cast<uint32_t>(b.scaled) << 25 |
+         static_cast<uint32_t>(b.pick) << 26;
 }
 __device__ inline ModBlock unpack_block(uint32_t v) {
   return ModBlock{static_cast<uint16_t>(v & 0x3ffu), static_cast<uint8_t>((v >> 10) & 0xffu),
                   static_cast<uint8_t>((v >> 18) & 0x3fu), static_cast<uint8_t>((v >> 24) & 1u),
-                  static_cast<uint8_t>((v >> 25) & 1u)};
+                  static_cast<uint8_t>((v >> 25) & 1u), static_cast<uint8_t>(v >> 26)};
 }
 
 struct SplitOperand {
@@ -172,6 +173,23 @@ __device__ inline void direct_panels(const Words& words, const float (&sgn)[4], 
       put(s[0][j] + s[0][l], s[1][j] + s[1][l], s[2][j] + s[2][l], s[3][j] + s[3][l]);
 }
 
+// One sub-digit of a digit (blk.pick - 1; blk.scaled: the top one, which takes the rest).
+template <class Words>
+__device__ inline void sub_digit_panel(const Words& words, const float (&sgn)[4], ModBlock blk,
+                                       int8_t* __restrict__ out, bool store) {
+  uint32_t f[4], v[4];
+  words.get(blk.lo, f);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int32_t d = static_cast<int32_t>(f[i] & ((1u << blk.bits) - 1u));
+    int32_t x = sgn[i] < 0.0f ? -d : d;
+    for (int j = 1; j < blk.pick; ++j) x = (x + 64) >> 7;  // (x - balanced(x)) / 128
+    if (!blk.scaled) x = static_cast<int32_t>(static_cast<uint32_t>(x) << 25) >> 25;
+    v[i] = static_cast<uint32_t>(x);
+  }
+  if (store) *reinterpret_cast<uint32_t*>(out) = pack4(v[0], v[1], v[2], v[3]);
+}
+
 // The panels p0 .. p1 - 1 of the operand, all its blocks in turn.
 template <class Words>
 __device__ inline void all_panels(const Words& words, const float (&sgn)[4], const uint32_t* __restrict__ blocks,
@@ -188,7 +206,8 @@ __device__ inline void all_panels(const Words& words, const float (&sgn)[4], con
         else residue_panels<6>(words, sgn, blk, c0, c1, out, kp, store);
       }
     } else if (first >= p0 && first < p1) {  // a digit's panels go together
-      if (blk.count == 1) direct_panels<1>(words, sgn, blk, out, kp, store);
+      if (blk.pick) sub_digit_panel(words, sgn, blk, out, store);
+      else if (blk.count == 1) direct_panels<1>(words, sgn, blk, out, kp, store);
       else if (blk.count == 3) direct_panels<2>(words, sgn, blk, out, kp, store);
       else if (blk.count == 6) direct_panels<3>(words, sgn, blk, out, kp, store);
       else direct_panels<4>(words, sgn, blk, out, kp, store);
@@ -291,19 +310,20 @@ hipError_t launch_split_tile(SplitArgs& a, hipStream_t stream) {
 
 hipError_t launch_modular_split(int64_t m, int64_t n, int64_t k, int L, int S, int w, const double* A,
                                 const double* B, const int32_t* EA, const int32_t* EB, int8_t* DA, int8_t* DB,
-                                const ModPlan& pl, hipStream_t stream) {
+                                const std::vector<ModBlock>& ba, int pa, const std::vector<ModBlock>& bb, int pb,
+                                hipStream_t stream) {
   if (m == 0 || n == 0 || k == 0) return hipSuccess;
-  if (pl.a.size() > static_cast<size_t>(kModMaxBlocks) || pl.b.size() > static_cast<size_t>(kModMaxBlocks))
+  if (ba.size() > static_cast<size_t>(kModMaxBlocks) || bb.size() > static_cast<size_t>(kModMaxBlocks))
     return hipErrorInvalidValue;
   SplitArgs a{};
   a.K = k;
   a.kp = mod_kp(k);
   a.L = L;
   a.gbits = w * S;
-  a.op[0] = SplitOperand{m, k, 1, m * k, pl.pa * a.kp, A, EA, DA, 0, static_cast<int>(pl.a.size()), pl.pa, 0};
-  a.op[1] = SplitOperand{n, 1, n, k * n, pl.pb * a.kp, B, EB, DB, 0, static_cast<int>(pl.b.size()), pl.pb, 0};
-  std::transform(pl.a.begin(), pl.a.end(), a.b[0], pack_block);
-  std::transform(pl.b.begin(), pl.b.end(), a.b[1], pack_block);
+  a.op[0] = SplitOperand{m, k, 1, m * k, pa * a.kp, A, EA, DA, 0, static_cast<int>(ba.size()), pa, 0};
+  a.op[1] = SplitOperand{n, 1, n, k * n, pb * a.kp, B, EB, DB, 0, static_cast<int>(bb.size()), pb, 0};
+  std::transform(ba.begin(), ba.end(), a.b[0], pack_block);
+  std::transform(bb.begin(), bb.end(), a.b[1], pack_block);
   const int bits = w * S, words = (bits + 52 + 63) / 64;
   if (L <= 2 && bits <= 128) return launch_split_tile<2, 2, 128, 2>(a, stream);
   if (L <= 4 && bits <= 256) return launch_split_tile<4, 4, 128, 4>(a, stream);

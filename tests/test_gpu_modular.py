@@ -135,3 +135,28 @@ def test_library_buffer_capture_and_a_small_workspace():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(C, md.mdgemm_ex(A, B, flags=md.MDGEMM_STAGED))
+
+
+@pytest.mark.parametrize("L,m,n,k,opts", [
+    (2, 1283, 1409, 130, {}), (2, 1100, 900, 257, {"cutoff": ALL}), (3, 1025, 1023, 127, {}),
+    (2, 1409, 1283, 300, {"slice_bits": 20}), (2, 1409, 1500, 200, {"slice_bits": 21}),
+    (2, 1283, 1300, 200, {"slice_bits": 7}), (8, 520, 700, 100, {}), (2, 900, 1000, 200, {"range_bits": 60}),
+])
+def test_a_readable_workspace_holds_digits_and_levels(L, m, n, k, opts):
+    """Without MDGEMM_WORKSPACE_SCRATCH the workspace holds the exponents, digit panels and
+    level planes of the pair schedule, whichever matrix cores formed the levels: every
+    byte of them equals the FP64 path's."""
+    print(f"[case] readable workspace L={L} {m}x{n}x{k} {opts}", flush=True)
+    A, B = _operands(L, m, n, k, m + n, spread=6)
+    lay = md.mdgemm_workspace_layout(m, n, k, L, **opts)
+    assert lay["direct_levels"] == 1
+    need = md.mdgemm_workspace_bytes(m, n, k, L, **opts)
+    ws = [torch.full((need,), fill, dtype=torch.uint8, device=DEV) for fill in (0x5a, 0x33)]
+    got = md.mdgemm_ex(A, B, workspace=ws[0], **opts)
+    want = md.mdgemm_ex(A, B, workspace=ws[1], flags=md.MDGEMM_STAGED, **opts)
+    assert torch.equal(got, want)
+    parts = [md.workspace_parts(ws[0], m, n, k, L, **opts),
+             md.workspace_parts(ws[1], m, n, k, L, flags=md.MDGEMM_STAGED, **opts)]
+    for name in ("EA", "EB", "DA", "DB", "G"):
+        assert torch.equal(parts[0][name], parts[1][name]), name
+    assert not torch.signbit(parts[0]["G"][parts[0]["G"] == 0]).any().item()
