@@ -501,11 +501,20 @@ bool small_plan(int64_t m, int64_t n, int64_t k, int limbs, const Resolved& r, i
 // workspace marked MDGEMM_WORKSPACE_SCRATCH) and the estimated time is below that
 // of the path that would run otherwise.  Not with MDGEMM_STAGED, the shortest
 // Karatsuba schedule, grouped or int8-digit products.
-constexpr double kModularBaseUs = 48.0;  // its six launches and their gaps
+constexpr double kModularBaseUs = 48.0;  // its launches and their gaps
+// The products of int8 digits level by level (MDGEMM_INT8): every pair one product,
+// an int32 plane per level, and splits that store single bytes (1.0 ps per panel byte
+// measured at 3001 x 4097 x 2999, 15 digits).
+double int8_estimate_us(int64_t m, int64_t n, int64_t k, int S, int T) {
+  const double mt = static_cast<double>(mdg::i8_rows(m)), nt = static_cast<double>(mdg::i8_rows(n));
+  const double kp = static_cast<double>(mdg::i8_kp(k)), mn = static_cast<double>(m) * static_cast<double>(n);
+  return 55.0 + 1e6 * (2.0 * mt * nt * kp * pair_count(S, T) / 2.6e15 + (T + 1) * 8.0 * mn / 4.5e12 +
+                       1.0e-12 * S * static_cast<double>(m + n) * static_cast<double>(k));
+}
 std::shared_ptr<const mdg::ModPlan> modular_for(int64_t m, int64_t n, int64_t k, int limbs, const Resolved& r,
                                                 bool scratch) {
   if (!scratch || (r.kind != Kind::kLevels && r.kind != Kind::kKaratsuba) ||
-      (r.flags & (MDGEMM_INT8 | MDGEMM_STAGED | MDGEMM_KARATSUBA_MIN_TERMS)) || r.Ge > 1 || r.sign)
+      (r.flags & (MDGEMM_STAGED | MDGEMM_KARATSUBA_MIN_TERMS)) || r.Ge > 1 || r.sign)
     return nullptr;
   if (mdg::accum_words(r.T + 1, r.w) > mdg::kModMaxWords || m > (int64_t{1} << 27) || n > (int64_t{1} << 27))
     return nullptr;
@@ -515,7 +524,9 @@ std::shared_ptr<const mdg::ModPlan> modular_for(int64_t m, int64_t n, int64_t k,
   int kc = 0;
   mdg::SmallLevelOwners owners{};
   double us = 0.0;
-  if (!small_plan(m, n, k, limbs, r, &kc, &owners, &us))
+  if (r.flags & MDGEMM_INT8)
+    us = int8_estimate_us(m, n, k, r.S, r.T);
+  else if (!small_plan(m, n, k, limbs, r, &kc, &owners, &us))
     us = staged_estimate_us(m, n, k, r.T, max_pairs(r.S, r.T), pair_count(r.S, r.T));
   return kModularBaseUs + 1e6 * pl->seconds < us ? pl : nullptr;
 }
@@ -970,14 +981,14 @@ size_t mdgemm_workspace_bytes(int64_t m, int64_t n, int64_t k, int limbs, const 
   Resolved r;
   if (m < 0 || n < 0 || k < 0 || resolve(limbs, m, n, k, opts, &r) != MDGEMM_OK) return SIZE_MAX;
   if (m == 0 || n == 0 || k == 0) return 0;
-  if (r.flags & MDGEMM_INT8) {
-    LayoutI8 L8;
-    return layout_int8(m, n, k, r.S, r.T, &L8) ? L8.total : SIZE_MAX;
-  }
   if (r.flags & MDGEMM_WORKSPACE_SCRATCH) {
     LayoutMod lm;
     const auto mod = resolved_exact(r, k) ? modular_for(m, n, k, limbs, r, true) : nullptr;
     if (mod && layout_modular(m, n, k, *mod, &lm)) return lm.total;
+  }
+  if (r.flags & MDGEMM_INT8) {
+    LayoutI8 L8;
+    return layout_int8(m, n, k, r.S, r.T, &L8) ? L8.total : SIZE_MAX;
   }
   Layout L;
   if (!layout(m, n, k, *planned_for(r.S, r.T, m, n, k, r.w, r.kind, group_code(r)), r.w, &L)) return SIZE_MAX;
@@ -1044,22 +1055,27 @@ int ex_impl(int64_t m, int64_t n, int64_t k, int limbs, const double* A, const d
     return MDGEMM_OK;
   }
 
-  if (r.flags & MDGEMM_INT8) {
-    *path = "int8 levels";
-    return run_int8(m, n, k, limbs, A, B, C, opts, r);
-  }
-  // the int8 products, when the workspace is scratch and holds them (else the
-  // paths below, in the workspace they always took)
+  // the int8 products, when the workspace is scratch (always with MDGEMM_INT8, whose
+  // workspace no call describes) and holds them; else the paths below, in the
+  // workspace they always took
   const bool caller_ws = opts && opts->workspace;
-  const auto mod = modular_for(m, n, k, limbs, r, !caller_ws || (r.flags & MDGEMM_WORKSPACE_SCRATCH));
+  const auto mod = modular_for(m, n, k, limbs, r,
+                               !caller_ws || (r.flags & (MDGEMM_WORKSPACE_SCRATCH | MDGEMM_INT8)));
   LayoutMod lm;
+  size_t taken = 0;  // of the caller workspace: what the other path would check as well
+  if (caller_ws && (r.flags & MDGEMM_INT8) && !(r.flags & MDGEMM_WORKSPACE_SCRATCH)) {
+    LayoutI8 l8;
+    if (!layout_int8(m, n, k, r.S, r.T, &l8)) return MDGEMM_EINVAL;
+    if (opts->workspace_bytes < l8.total) return MDGEMM_EWORKSPACE;
+    taken = l8.total;
+  }
   if (mod && layout_modular(m, n, k, *mod, &lm) && (!caller_ws || opts->workspace_bytes >= lm.total)) {
     *path = "int8 residues";
     char* ws = nullptr;
     LibraryBuffer lib;
     int st = MDGEMM_OK;
     if (caller_ws) {
-      if (workspace_overlaps(opts->workspace, lm.total, m, n, k, limbs, A, B, C)) return MDGEMM_EINVAL;
+      if (workspace_overlaps(opts->workspace, std::max(lm.total, taken), m, n, k, limbs, A, B, C)) return MDGEMM_EINVAL;
       ws = static_cast<char*>(opts->workspace);
     } else {
       st = lib.acquire(lm.total, s, &ws);
@@ -1071,6 +1087,10 @@ int ex_impl(int64_t m, int64_t n, int64_t k, int limbs, const double* A, const d
     }
     if (st != MDGEMM_ENOMEM && st != MDGEMM_EINVAL) return st;  // no room, or capturing: the paths below
     *path = "refused";
+  }
+  if (r.flags & MDGEMM_INT8) {
+    *path = "int8 levels";
+    return run_int8(m, n, k, limbs, A, B, C, opts, r);
   }
   const auto pl = planned_for(r.S, r.T, m, n, k, r.w, r.kind, group_code(r));
   if (!schedule_exact(pl->s, k, r.w)) return MDGEMM_EEXACT;

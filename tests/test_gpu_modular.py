@@ -78,6 +78,18 @@ def test_limbs_equal_the_fp64_level_products(L, m, n, k, opts):
     assert torch.equal(got, want)
 
 
+@pytest.mark.parametrize("L,m,n,k,opts", [(2, 300, 700, 500, {}), (3, 600, 500, 300, {}),
+                                          (3, 513, 600, 200, {"slice_bits": 5}), (2, 400, 400, 300, {"range_bits": 40})])
+def test_int8_digits(L, m, n, k, opts):
+    """MDGEMM_INT8 chooses the digits; their products equal the FP64 path's at those digits."""
+    print(f"[case] int8 digits L={L} {m}x{n}x{k} {opts}", flush=True)
+    assert _modular(m, n, k, L, flags=md.MDGEMM_INT8, **opts)
+    A, B = _operands(L, m, n, k, 7 * m, spread=4)
+    w, S, T = md.mdgemm_plan(m, n, k, L, flags=md.MDGEMM_INT8, **opts)
+    want = md.mdgemm_ex(A, B, slice_bits=w, slices=S, cutoff=T, flags=md.MDGEMM_STAGED)
+    assert torch.equal(md.mdgemm_ex(A, B, flags=md.MDGEMM_INT8, **opts), want)
+
+
 @pytest.mark.parametrize("L,m,n,k,opts", [(2, 260, 258, 130, {}), (4, 257, 300, 33, {"cutoff": ALL})])
 def test_limbs_equal_the_oracle(L, m, n, k, opts):
     print(f"[case] oracle L={L} {m}x{n}x{k} {opts}", flush=True)
