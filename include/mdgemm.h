@@ -485,7 +485,8 @@ size_t mdgemm_qr_dd_workspace_bytes(int64_t m, int64_t n, int nb);
  * each panel's reflections are accumulated as I - V T V^T (T upper triangular)
  * and the columns to its right updated as A2 - V (T^T (V^T A2)), three products
  * on mdgemm_ex at the adaptive digit width.  workspace: caller-owned device buffer of
- * mdgemm_qr_dd_workspace_bytes() bytes, not overlapping A or tau.  Stream
+ * mdgemm_qr_dd_workspace_bytes() bytes, not overlapping A or tau; one that holds the
+ * products' FP64 panels and levels only does too, the results are the same.  Stream
  * ordered; returns MDGEMM_OK, MDGEMM_EINVAL, MDGEMM_EWORKSPACE or a status of
  * mdgemm_ex.  Inputs must be finite and normalized double-doubles. */
 int mdgemm_qr_dd(int64_t m, int64_t n, int nb, double* A, double* tau, void* workspace, size_t workspace_bytes,
@@ -510,7 +511,8 @@ size_t mdgemm_taylor_dd_workspace_bytes(int64_t n, int64_t r, int d);
  * into M = R^-1 Q^T; then for each degree X_k = M (B_k - [A_k ... A_1]
  * [X_0; ...; X_{k-1}]), two products on mdgemm_ex at the adaptive digit width.
  * workspace: caller-owned device buffer of mdgemm_taylor_dd_workspace_bytes()
- * bytes, overlapping none of A, B and X; X overlaps neither A nor B.  Stream
+ * bytes (or room for the FP64 products only, as mdgemm_qr_dd), overlapping none of
+ * A, B and X; X overlaps neither A nor B.  Stream
  * ordered; returns MDGEMM_OK, MDGEMM_EINVAL, MDGEMM_EWORKSPACE or a status of
  * mdgemm_ex.  Inputs must be finite and normalized double-doubles. */
 int mdgemm_taylor_dd(int64_t n, int64_t r, int d, const double* A, const double* B, double* X, void* workspace,

@@ -7,6 +7,7 @@
 
 #include <vector>
 
+#include "mdgemm.h"
 #include "modular.h"
 #include "schedule.h"
 
@@ -218,7 +219,14 @@ hipError_t launch_set_i32(int32_t* p, int64_t count, int32_t value, hipStream_t 
 // written).  Panels of nb <= 64 columns.  qr_core_workspace gives the bytes of
 // the workspace qr_core takes (SIZE_MAX for invalid sizes); qr_core checks no
 // overlaps and returns an mdgemm status.
-size_t qr_core_workspace(int64_t m, int64_t nf, int64_t n, int nb);
-int qr_core(int64_t m, int64_t nf, int64_t n, int nb, double* A, double* tau, void* workspace, hipStream_t s);
+// With `least` both lay the workspace out for the products' FP64 panels and levels
+// only; without, for the int8 products as well, where these are the faster ones.
+size_t qr_core_workspace(int64_t m, int64_t nf, int64_t n, int nb, bool least);
+int qr_core(int64_t m, int64_t nf, int64_t n, int nb, double* A, double* tau, void* workspace, bool least,
+            hipStream_t s);
+
+// Workspace of one of their products (double-double, MDGEMM_WORKSPACE_SCRATCH in o):
+// what any path takes, or with `least` what the FP64 ones take.
+size_t product_workspace(int64_t m, int64_t n, int64_t k, mdgemm_opts o, bool least);
 
 }  // namespace mdg

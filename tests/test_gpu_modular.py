@@ -172,3 +172,59 @@ def test_a_readable_workspace_holds_digits_and_levels(L, m, n, k, opts):
     for name in ("EA", "EB", "DA", "DB", "G"):
         assert torch.equal(parts[0][name], parts[1][name]), name
     assert not torch.signbit(parts[0]["G"][parts[0]["G"] == 0]).any().item()
+
+
+def _least(total, shapes):
+    """A QR's or Taylor series' workspace without room for the int8 products: the size with
+    its part for the products (the largest need of `shapes`) replaced."""
+    up = lambda x: (x + 255) // 256 * 256  # noqa: E731
+    plain = [md.mdgemm_workspace_bytes(*s, 2, slice_bits=-1) for s in shapes]
+    full = [md.mdgemm_workspace_bytes(*s, 2, slice_bits=-1, flags=md.MDGEMM_WORKSPACE_SCRATCH) for s in shapes]
+    return total - up(max(plain + full)) + up(max(plain))
+
+
+def _panels(m, nf, n, nb=64):
+    for j0 in range(0, nf, nb):
+        jb = min(nb, nf - j0)
+        mp, nc = m - j0, n - j0 - jb
+        if nc:
+            yield from ((jb, nc, mp), (jb, nc, jb), (mp, nc, jb))
+
+
+@pytest.mark.parametrize("m,n", [(700, 640), (1027, 517), (1030, 1030)])
+def test_qr_in_both_workspaces(m, n):
+    """The trailing products on either matrix cores: the same factors, bit for bit."""
+    need = int(md.lib().mdgemm_qr_dd_workspace_bytes(m, n, 64))
+    least = _least(need, list(_panels(m, n, n)))
+    print(f"[case] qr {m}x{n}: {need} or {least} bytes", flush=True)
+    A, _ = _operands(2, m, 8, n, m + n)
+    A[0, 0, :] = 1.0
+    A[:, :, n - 1] = A[:, :, 0]
+    got = [md.mdgemm_qr_dd(A.clone(), workspace=torch.empty(size, dtype=torch.uint8, device=DEV))
+           for size in (need, least)]
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    work, tau, ws = A.clone(), torch.empty(2, n, dtype=torch.float64, device=DEV), torch.empty(need, dtype=torch.uint8, device=DEV)
+    assert md.lib().mdgemm_qr_dd(m, n, 64, work.data_ptr(), tau.data_ptr(), ws.data_ptr(), least - 1,
+                                 None) == md.MDGEMM_EWORKSPACE
+    assert torch.equal(work, A)
+
+
+@pytest.mark.parametrize("n,r,d", [(300, 20, 3), (513, 64, 2)])
+def test_taylor_in_both_workspaces(n, r, d):
+    need = int(md.lib().mdgemm_taylor_dd_workspace_bytes(n, r, d))
+    qr = list(_panels(n, n, 2 * n))
+    own = [(n, r, n)] + [(min(64, n - j), n, n - j - 64) for j in range(0, n - 64, 64)]
+    own += [(n, r, k * n) for k in range(1, d + 1)]
+    least = _least(_least(need, qr), own)
+    print(f"[case] taylor n={n} r={r} d={d}: {need} or {least} bytes", flush=True)
+    gen = torch.Generator().manual_seed(n)
+    A = torch.randn(d + 1, 2, n, n, dtype=torch.float64, generator=gen)
+    A[:, 1] *= 2.0 ** -56
+    A[0, 0] += 4 * n ** 0.5 * torch.eye(n, dtype=torch.float64)
+    B = torch.randn(d + 1, 2, n, r, dtype=torch.float64, generator=gen)
+    B[:, 1] *= 2.0 ** -56
+    A, B = A.to(DEV), B.to(DEV)
+    got = [md.mdgemm_taylor_dd(A, B, workspace=torch.empty(size, dtype=torch.uint8, device=DEV))
+           for size in (need, least)]
+    assert torch.isfinite(got[0]).all()
+    assert torch.equal(got[0], got[1])
