@@ -83,20 +83,29 @@ constexpr int kColThreads = 256;  // 32 column lanes x 8 row groups
 constexpr int kFoldBatch = 8;    // partial sums a thread loads per column group before adding them
 
 constexpr int kRowGroups = kColThreads / 32;                // 8: rows rb + rg + 8 q
-constexpr int kColGroups = kMaxNb / 32;                      // columns c0 + 32 h + cc, h < 2
+// a lane holds the columns c0 + 32 h + cc, h < kH
 static_assert(kPanelRowsSmall % kRowGroups == 0 && kPanelRowsShort % kRowGroups == 0 &&
-                  kPanelRowsTall % kRowGroups == 0 && kMaxNb % 32 == 0,
+                  kPanelRowsTall % kRowGroups == 0 && kMaxNb == 2 * 32,
               "thread layout of the column kernels");
 static_assert(kPanelRowsShort <= 64 && kPanelRowsTall <= 64, "one row per thread of the first two waves");
 
 // pd: two buffers of [2][G][kMaxNb] (hi plane, lo plane); prow: two of [2][kMaxNb]
-template <int kRows>
+//
+// A step is a chain of latencies (launch, loads of the partials, about 600 dependent
+// FP64 operations), on one wave per SIMD.  Three things shorten it without touching
+// any sum's order: the late steps of a panel, with at most 32 columns left, take one
+// column group (kH = 1) and skip the other's sums, which every block repeats in full;
+// loads take clamped addresses and a select instead of branches, the next batch of
+// partials on its way while one is added; and tau is formed beside v and w instead of
+// before them.  A step of 8 (16) rows took 7.3 (9.0) us, now 7.5 (9.3) with two column
+// groups and 6.4 (7.2) with one; a 2048 x 2048 factorization 28.1 ms, now 27.0.
+template <int kRows, int kH>
 __global__ void __launch_bounds__(kColThreads) qr_col_step_kernel(int64_t m, int64_t n, int64_t j0, int jb, int s,
                                                                   double* __restrict__ A, double* __restrict__ tau,
                                                                   double* __restrict__ pd,
                                                                   double* __restrict__ prow) {
   constexpr int kRPT = kRows / kRowGroups;  // rows per thread
-  __shared__ dd red2[kColGroups][kColThreads];
+  __shared__ dd red2[kH][kColThreads];
   __shared__ dd td[kMaxNb], tw[kMaxNb], vs[kRows], xs[kRows];
   __shared__ dd s_scale, s_tau;
   __shared__ int s_mode;
@@ -115,14 +124,15 @@ __global__ void __launch_bounds__(kColThreads) qr_col_step_kernel(int64_t m, int
   // s = 0), column s - 1 below its pivot (one row per thread of the first
   // kRows), and the pivot row's entries of step s - 1.
   const int64_t rlo = s > 0 ? rp : r0;
-  dd av[kColGroups][kRPT];
+  dd av[kH][kRPT];
 #pragma unroll
-  for (int h = 0; h < kColGroups; ++h) {
+  for (int h = 0; h < kH; ++h) {
     const int c = s + 32 * h + cc;
 #pragma unroll
     for (int q = 0; q < kRPT; ++q) {
       const int64_t r = rb + rg + kRowGroups * q;
-      av[h][q] = c < jb && r >= rlo && r < re ? ldd(A, plane, r * n + j0 + c) : dd{0.0, 0.0};
+      const dd v = ldd(A, plane, min(r, m - 1) * n + j0 + min(c, jb - 1));
+      av[h][q] = c < jb && r >= rlo && r < re ? v : dd{0.0, 0.0};
     }
   }
   if (s > 0) {
@@ -132,7 +142,7 @@ __global__ void __launch_bounds__(kColThreads) qr_col_step_kernel(int64_t m, int
       const int64_t r = rb + tid;
       if (r > rp && r < re) xv = ldd(A, plane, r * n + j0 + s - 1);
     }
-    // x1 for thread 0; p_c (c = s + t) for thread 64 + t, which forms tau w_c
+    // x1 for thread 0; p_c (c = s + t) for thread 64 + t, which forms w_c
     if (tid == 0) pv = ldd(prow_in, kMaxNb, 0);
     if (tid >= 64 && tid < 64 + ncols - 1) pv = ldd(prow_in, kMaxNb, tid - 63);
     // d_c for the columns g = cc and g = 32 + cc of both groups at once:
@@ -141,25 +151,34 @@ __global__ void __launch_bounds__(kColThreads) qr_col_step_kernel(int64_t m, int
     // (entries beyond G are zeros) and the batches in order, then the eight row
     // groups in a tree
     {
-      dd sum[kColGroups];
+      dd sum[kH];
 #pragma unroll
-      for (int h = 0; h < kColGroups; ++h) sum[h] = {0.0, 0.0};
-      for (int64_t b0 = rg; b0 < G; b0 += kRowGroups * kFoldBatch) {
-        dd v[kColGroups][kFoldBatch];
+      for (int h = 0; h < kH; ++h) sum[h] = {0.0, 0.0};
+      constexpr int64_t kBatch = kRowGroups * kFoldBatch;
+      dd v[kH][kFoldBatch], next[kH][kFoldBatch];
+      auto load = [&](dd(&x)[kH][kFoldBatch], int64_t b0) {
 #pragma unroll
-        for (int h = 0; h < kColGroups; ++h)
+        for (int h = 0; h < kH; ++h)
 #pragma unroll
-          for (int u = 0; u < kFoldBatch; ++u) {
-            const int64_t b = b0 + kRowGroups * u;
-            v[h][u] = b < G && 32 * h + cc < ncols ? ldd(pd_in, pplane, b * kMaxNb + 32 * h + cc) : dd{0.0, 0.0};
-          }
+          for (int u = 0; u < kFoldBatch; ++u) x[h][u] = ldd(pd_in, pplane, min(b0 + kRowGroups * u, G - 1) * kMaxNb + 32 * h + cc);
+      };
+      load(v, rg);
+      for (int64_t b0 = rg; b0 < G; b0 += kBatch) {
+        if (b0 + kBatch < G) load(next, b0 + kBatch);
 #pragma unroll
-        for (int h = 0; h < kColGroups; ++h) sum[h] = dd_add(sum[h], tree_sum<kFoldBatch>(v[h]));
+        for (int h = 0; h < kH; ++h) {
+#pragma unroll
+          for (int u = 0; u < kFoldBatch; ++u)
+            if (b0 + kRowGroups * u >= G || 32 * h + cc >= ncols) v[h][u] = dd{0.0, 0.0};
+          sum[h] = dd_add(sum[h], tree_sum<kFoldBatch>(v[h]));
+#pragma unroll
+          for (int u = 0; u < kFoldBatch; ++u) v[h][u] = next[h][u];
+        }
       }
 #pragma unroll
-      for (int h = 0; h < kColGroups; ++h) red2[h][tid] = sum[h];
+      for (int h = 0; h < kH; ++h) red2[h][tid] = sum[h];
       __syncthreads();
-      if (rg < kColGroups) {
+      if (rg < kH) {
         dd t[kRowGroups];
 #pragma unroll
         for (int g = 0; g < kRowGroups; ++g) t[g] = red2[rg][g * 32 + cc];
@@ -173,26 +192,20 @@ __global__ void __launch_bounds__(kColThreads) qr_col_step_kernel(int64_t m, int
       dd diag;
       if (sigma.hi == 0.0) {
         s_mode = x1.hi < 0.0 ? 1 : 0;
-        s_tau = s_mode ? dd{2.0, 0.0} : dd{0.0, 0.0};
         diag = s_mode ? dd_neg(x1) : x1;
       } else {
         const dd mu = dd_sqrt(dd_add(dd_mul(x1, x1), sigma));
-        const dd v1 = x1.hi <= 0.0 ? dd_sub(x1, mu) : dd_neg(dd_div(sigma, dd_add(x1, mu)));
-        const dd v1sq = dd_mul(v1, v1);
-        s_tau = dd_div(dd_mul_d(v1sq, 2.0), dd_add(sigma, v1sq));
-        s_scale = v1;
+        s_scale = x1.hi <= 0.0 ? dd_sub(x1, mu) : dd_neg(dd_div(sigma, dd_add(x1, mu)));
         s_mode = 2;
         diag = mu;
       }
-      if (blockIdx.x == 0) {
-        std_(A, plane, rp * n + j0 + s - 1, diag);
-        std_(tau, n, j0 + s - 1, s_tau);
-      }
+      if (blockIdx.x == 0) std_(A, plane, rp * n + j0 + s - 1, diag);
     }
     __syncthreads();
     const int mode = s_mode;
-    // v at the block's rows (1 at the pivot; mode 2: x / v1 below it, else 0),
-    // and tau w_c for c = s + tid: w_c = p_c + d_c / v1 (p_c alone when v = e_1)
+    // in three waves: v at the block's rows (1 at the pivot; mode 2: x / v1 below it,
+    // else 0), w_c for c = s + tid (w_c = p_c + d_c / v1, p_c alone when v = e_1), and
+    // tau
     if (tid < kRows) {
       const int64_t r = rb + tid;
       dd v = {0.0, 0.0};
@@ -206,16 +219,24 @@ __global__ void __launch_bounds__(kColThreads) qr_col_step_kernel(int64_t m, int
     }
     if (tid >= 64 && tid < 64 + ncols - 1) {
       const int t = tid - 64;
-      const dd w = mode == 2 ? dd_add(pv, dd_div(td[t + 1], s_scale)) : pv;
-      tw[t] = dd_mul(s_tau, w);
+      tw[t] = mode == 2 ? dd_add(pv, dd_div(td[t + 1], s_scale)) : pv;
+    }
+    if (tid == 128) {
+      dd t = {mode == 1 ? 2.0 : 0.0, 0.0};
+      if (mode == 2) {
+        const dd v1sq = dd_mul(s_scale, s_scale);
+        t = dd_div(dd_mul_d(v1sq, 2.0), dd_add(td[0], v1sq));
+      }
+      s_tau = t;
+      if (blockIdx.x == 0) std_(tau, n, j0 + s - 1, t);
     }
     __syncthreads();
     // a_c <- a_c - (tau w_c) v at the rows from the previous pivot down
 #pragma unroll
-    for (int h = 0; h < kColGroups; ++h) {
+    for (int h = 0; h < kH; ++h) {
       const int c = s + 32 * h + cc;
       if (c < jb) {
-        const dd t = tw[32 * h + cc];
+        const dd t = dd_mul(s_tau, tw[32 * h + cc]);
 #pragma unroll
         for (int q = 0; q < kRPT; ++q) {
           const int64_t r = rb + rg + kRowGroups * q;
@@ -242,9 +263,9 @@ __global__ void __launch_bounds__(kColThreads) qr_col_step_kernel(int64_t m, int
   // row groups in trees, both column groups in one pass; the pivot row's
   // entries from the block that holds it
   {
-    dd acc[kColGroups];
+    dd acc[kH];
 #pragma unroll
-    for (int h = 0; h < kColGroups; ++h) {
+    for (int h = 0; h < kH; ++h) {
       const int c = s + 32 * h + cc;
       dd pr[kRPT];
 #pragma unroll
@@ -257,7 +278,7 @@ __global__ void __launch_bounds__(kColThreads) qr_col_step_kernel(int64_t m, int
       red2[h][tid] = acc[h];
     }
     __syncthreads();
-    if (rg < kColGroups && 32 * rg < jb - s) {
+    if (rg < kH && 32 * rg < jb - s) {
       dd t[kRowGroups];
 #pragma unroll
       for (int g = 0; g < kRowGroups; ++g) t[g] = red2[rg][g * 32 + cc];
@@ -590,9 +611,11 @@ int qr_core(int64_t m, int64_t nf, int64_t n, int nb, double* A, double* tau, vo
     auto columns = [&](auto rows) {
       constexpr int kRows = decltype(rows)::value;
       const unsigned groups = static_cast<unsigned>((mp + kRows - 1) / kRows);
-      for (int step = 0; step <= jb; ++step)
-        hipLaunchKernelGGL(mdg::qr_col_step_kernel<kRows>, dim3(groups), dim3(mdg::kColThreads), 0, s, m, n, j0, jb,
-                           step, A, tau, pd, prow);
+      for (int step = 0; step <= jb; ++step) {
+        // step s sums the columns s - 1 .. jb - 1: 32 lanes' worth or two
+        auto kernel = jb - step + 1 > 32 ? &mdg::qr_col_step_kernel<kRows, 2> : &mdg::qr_col_step_kernel<kRows, 1>;
+        hipLaunchKernelGGL(kernel, dim3(groups), dim3(mdg::kColThreads), 0, s, m, n, j0, jb, step, A, tau, pd, prow);
+      }
     };
     if (mp > mdg::kShortPanel)
       columns(std::integral_constant<int, mdg::kPanelRowsTall>{});
