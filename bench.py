@@ -2,18 +2,25 @@
 """Throughput of the multiple-double product C = A.B on one MI355X.
 
 One step = one ``mdgemm_ex`` call over the whole path (row/column exponents,
-exact splits of A and B, the level GEMMs on the FP64 matrix cores, exact
-accumulation and rounding), with A, B, C and the workspace resident in HBM.
+exact splits of A and B, the products of the digit pairs, exact accumulation and
+rounding), with A, B, C and the workspace resident in HBM.  The workspace is marked
+scratch (MDGEMM_WORKSPACE_SCRATCH), so the library forms the exact sum of the pairs
+on the int8 matrix cores where that is faster, with the same limbs as the FP64 level
+GEMMs; ``products`` says which ran.
 
 Prints one JSON line:
 * ``value``: effective multiple-double GFLOP/s = 2 m n k / (time per step);
-* ``roofline``: the level-GEMM kernel (the dominant one) against the FP64 MFMA
-  peak: algorithmic flops 2 m n k |pairs| per launch over its average duration
-  from HIP events recorded on the launch stream around it in every timed step;
+* ``roofline``: the FP64 level-GEMM kernel against the FP64 MFMA peak:
+  algorithmic flops 2 m n k |pairs| per launch over its average duration
+  from HIP events recorded on the launch stream around it in every timed step
+  (where the headline ran on the int8 matrix cores: in the steps of
+  ``fp64_products``, the same product with MDGEMM_STAGED);
   ``traffic`` is the HBM bytes per launch from the committed rocprofv3 counter
   summary of this kernel and workload, or null when the kernel source changed
   after the counters were taken;
-* ``stages``: every stage's average time and algorithmic rate;
+* ``stages``: every stage's average time and algorithmic rate (with int8 residue
+  products the times, and the products' rate as pair products per second:
+  2 m n k |pairs| over the GEMM stage, no fraction of a peak);
 * ``adaptive_width``: the same workload with the adaptive digit width (fewer,
   wider digits whose level sums stay exact at this k; at least the digit bits of
   four 13-bit digits per limb), timed over a few steps; the headline ``value``
@@ -31,11 +38,10 @@ Prints one JSON line:
 * ``exponent_classes`` (workloads with a range, c7): the same product grouped
   by exponent class over that range (section 3's balancing), timed over a few
   steps, with a sampled parity check against the oracle's grouped chain;
-* ``karatsuba`` (the Karatsuba schedule of the level products: fewer
-  products, bit-identical limbs) and ``int8`` (the level products of 7-bit
-  digits on the int8 matrix cores, within the same error bound), a few timed
-  steps each beside the headline, which keeps the paper's separate pair
-  products on the FP64 matrix cores;
+* ``karatsuba`` (the Karatsuba schedule of the level products on the FP64 matrix
+  cores: fewer products, bit-identical limbs) and ``int8`` (7-bit digits on the
+  int8 matrix cores, within the same error bound), a few timed steps each beside
+  the headline;
 * ``--extras`` adds ``karatsuba_adaptive``, ``sign_groups`` (section 3's
   sign grouping, four products, the same limbs), ``taylor_dd`` (the QR's
   application to power-series systems, timed) and ``qr_dd`` (the
@@ -395,6 +401,7 @@ def main(argv=None) -> int:
         and the C entry point called directly, so that a small product is not
         bound by the host), then K steps with the library's stage events
         (MDGEMM_TIME_STAGES, each step read back before the next)."""
+        base_flags |= md.MDGEMM_WORKSPACE_SCRATCH  # nothing here reads the workspace
         ws = torch.empty(max(1, md.mdgemm_workspace_bytes(w.m, w.n, w.k, w.limbs, flags=base_flags, **opts)),
                          dtype=torch.uint8, device=dev)
         o_plain = md.make_opts(flags=base_flags, stream=stream, workspace=ws, **opts)
@@ -428,6 +435,13 @@ def main(argv=None) -> int:
         del ws
         return ms, stage_sum / steps
 
+    def on_residues(opts, flags=0):
+        """True when the library forms the pairs by int8 residue products: a scratch
+        workspace then has another size."""
+        def need(f):
+            return md.mdgemm_workspace_bytes(w.m, w.n, w.k, w.limbs, flags=f, **opts)
+        return need(flags | md.MDGEMM_WORKSPACE_SCRATCH) != need(flags)
+
     bits_arg = md.MDGEMM_SLICE_BITS_AUTO if args.slice_bits == "auto" else int(args.slice_bits)
     sched_flags = md.MDGEMM_KARATSUBA if args.schedule == "karatsuba" else 0
     int8 = args.products == "int8"
@@ -437,6 +451,12 @@ def main(argv=None) -> int:
     bits, S, T = md.mdgemm_plan(w.m, w.n, w.k, w.limbs, flags=sched_flags, **opts)
     ms_per_step, stage_ms = measure(opts, args.steps, args.warmup, sched_flags)
     C_h = None if args.no_parity else C.cpu().numpy()  # the last timed step's product, for the parity check
+    residues = on_residues(opts, sched_flags)
+    head_ms = stage_ms  # the headline's stages; below, stage_ms are the digit products' (FP64, or int8 level by level)
+    fp64_ms = None
+    if residues and not int8:
+        fp64_ms, stage_ms = measure(opts, max(1, min(args.steps, args.adaptive_steps or 3)), 1,
+                                    sched_flags | md.MDGEMM_STAGED)
 
     if args.copy_probe_mib > 0:
         src = torch.ones(args.copy_probe_mib * (1 << 20) // 8, dtype=torch.float64, device=dev)
@@ -454,7 +474,7 @@ def main(argv=None) -> int:
     # launch), whose stages leave nothing in the workspace: the library refuses
     # to describe a workspace layout for them
     fused = False
-    if not int8 and not sched_flags:
+    if not int8 and not sched_flags and not residues:
         try:
             md.mdgemm_workspace_layout(w.m, w.n, w.k, w.limbs, **opts)
         except md.MdgemmError:
@@ -496,6 +516,10 @@ def main(argv=None) -> int:
                                    "in one launch",
                          "ops_per_step": roofline.pop("flops_per_launch"),
                          "avg_step_ms": roofline.pop("avg_launch_ms")})
+        if residues:
+            roofline.update({"kernel": "modular_gemm_kernel: the digit pairs by int8 residue products "
+                                       "(achieved: pair products, not the products run)",
+                             "frac": None, "peak": None})
     if fused:
         roofline.update({"kernel": "small_product_kernel (the five steps fused per 16 x 16 tile of C, "
                                    "v_mfma_f64_16x16x4f64)", "traffic": None})
@@ -509,9 +533,22 @@ def main(argv=None) -> int:
                          "bytes": bytes_acc},
         "hbm_peak_GB/s": HBM_PEAK_GBS,
     }
+    products = "int8 residues" if residues else "int8 levels" if int8 else "fp64 levels"
+    digit_stages = stages
+    if residues:
+        stages = {"exponents": dict(stages["exponents"]), "split": {"ms": round(head_ms[1], 4)},
+                  "residue_gemm": {"ms": round(head_ms[2], 4),
+                                   "pair_products_TFLOP/s": round(slice_flops / (head_ms[2] * 1e-3) / 1e12, 1)},
+                  "accum_renorm": {"ms": round(head_ms[3], 4)}, "hbm_peak_GB/s": HBM_PEAK_GBS}
+        stages["exponents"].update({"ms": round(head_ms[0], 4),
+                                    "GB/s": round(bytes_exp / (head_ms[0] * 1e-3) / 1e9, 1)})
+        if int8:
+            digit_stages = stages
     if fused:  # one kernel: its time is the level-product stage's, the others are event gaps
         stages = {"fused_small_product": {"ms": round(stage_ms[2], 4), "TFLOP/s": round(achieved, 3)},
                   "event_gaps_ms": [round(float(x), 4) for x in (stage_ms[0], stage_ms[1], stage_ms[3])]}
+        digit_stages = stages
+        products = "fused small product"
     config = {"workload": f"{w.name}: {w.description}", "m": m, "n": n, "k": k, "limbs": L, "slices": S,
               "cutoff": T, "pairs": pairs, "seed": w.seed, "panels": "f32" if panels_f32 else "f64"}
     if sched_flags and not int8:
@@ -542,10 +579,17 @@ def main(argv=None) -> int:
         "dtype": "int8" if int8 else "f64",
         "data": "synthetic",
         "config": config,
+        "products": products,
         "roofline": roofline,
         "stages": stages,
-        "slice_gemm_share": round(stage_ms[2] / stage_ms.sum(), 4),
+        "slice_gemm_share": round(head_ms[2] / head_ms.sum(), 4),
     }
+    if fp64_ms is not None:
+        # the same product with MDGEMM_STAGED: the digit pairs level by level on the FP64 matrix cores
+        out["fp64_products"] = {"ms_per_step": round(fp64_ms, 4),
+                                "value": round(md_flops / (fp64_ms * 1e-3) / 1e9, 3), "stages": digit_stages,
+                                "slice_gemm_share": round(stage_ms[2] / stage_ms.sum(), 4)}
+
     def extra(a_opts, flags):
         """A few timed steps of the same workload with other digit options or schedule."""
         a_bits, a_S, a_T = md.mdgemm_plan(m, n, k, L, flags=flags, **a_opts)
@@ -553,12 +597,15 @@ def main(argv=None) -> int:
         a_ms, a_stage = measure(a_opts, args.adaptive_steps, 2, flags)
         a_pairs = workloads.pair_count(a_S, a_T)
         a_tflops = 2.0 * m * n * k * a_info["terms"] / (a_stage[2] * 1e-3) / 1e12
+        a_res = on_residues(a_opts, flags) and not flags & md.MDGEMM_STAGED
         return {
             "slice_bits": a_bits, "slices": a_S, "cutoff": a_T, "pairs": a_pairs, "products": a_info["terms"],
             "planes": a_info["planes"], "steps": args.adaptive_steps, "ms_per_step": round(a_ms, 4),
             "value": round(md_flops / (a_ms * 1e-3) / 1e9, 3),
             "stage_ms": [round(float(x), 4) for x in a_stage],
-            "slice_gemm_TFLOP/s": round(a_tflops, 3), "frac": round(a_tflops / MFMA_F64_PEAK_TFLOPS, 4),
+            **({"on": "int8 residues", "pair_products_TFLOP/s": round(a_tflops, 1)} if a_res else
+               {"on": "fp64 levels", "slice_gemm_TFLOP/s": round(a_tflops, 3),
+                "frac": round(a_tflops / MFMA_F64_PEAK_TFLOPS, 4)}),
         }
 
     def int8_mode():
@@ -577,7 +624,8 @@ def main(argv=None) -> int:
             "steps": args.adaptive_steps, "ms_per_step": round(i_ms, 4),
             "value": round(md_flops / (i_ms * 1e-3) / 1e9, 3),
             "stage_ms": [round(float(x), 4) for x in i_stage],
-            "level_gemm_TOPS": round(tops, 1), "frac": round(tops / INT8_PEAK_TOPS, 4),
+            **({"on": "int8 residues", "pair_products_TOPS": round(tops, 1)} if on_residues(i_opts, I8) else
+               {"on": "int8 levels", "level_gemm_TOPS": round(tops, 1), "frac": round(tops / INT8_PEAK_TOPS, 4)}),
         }
 
     if not args.no_parity:
@@ -585,12 +633,13 @@ def main(argv=None) -> int:
     if not args.no_calibration:
         cal = calibrate(md, torch, dev, stream)
         out["calibration"] = cal
-        roofline["peak_measured"] = cal["mfma_f64_TFLOP/s"]
-        roofline["frac_of_measured"] = round(achieved / cal["mfma_f64_TFLOP/s"], 4)
+        if not int8:
+            roofline["peak_measured"] = cal["mfma_f64_TFLOP/s"]
+            roofline["frac_of_measured"] = round(achieved / cal["mfma_f64_TFLOP/s"], 4)
         # every memory-bound stage against the published 8 TB/s and against a
         # plain stream of its own size and read/write mix (planes of doubles,
         # the stage's read and write bytes per element rounded to whole planes)
-        if "split" in stages:
+        if "split" in digit_stages and not (int8 and residues):
             cnt_s = m * k + k * n
             w_split = bytes_split - 8.0 * L * cnt_s - 4.0 * (m + n)
             mixes = {"exponents": (cnt_s, 1, 0),
@@ -599,19 +648,20 @@ def main(argv=None) -> int:
                                                           (8.0 * m * n))), L)}
             probes = stage_probes(md, torch, dev, stream, mixes)
             for key, pr in probes.items():
-                stages[key]["frac_of_peak"] = round(stages[key]["GB/s"] / HBM_PEAK_GBS, 4)
-                stages[key]["probe_GB/s"] = pr["GB/s"]
-                stages[key]["frac_of_probe"] = round(stages[key]["GB/s"] / pr["GB/s"], 4)
-                stages[key]["probe_mix"] = f"{pr['reads']} read + {pr['writes']} write planes of {pr['count']}"
+                digit_stages[key]["frac_of_peak"] = round(digit_stages[key]["GB/s"] / HBM_PEAK_GBS, 4)
+                digit_stages[key]["probe_GB/s"] = pr["GB/s"]
+                digit_stages[key]["frac_of_probe"] = round(digit_stages[key]["GB/s"] / pr["GB/s"], 4)
+                digit_stages[key]["probe_mix"] = f"{pr['reads']} read + {pr['writes']} write planes of {pr['count']}"
     if bits_arg == 13 and not sched_flags and args.adaptive_steps > 0:
         # the same workload with the adaptive width reported beside the paper's
         # 13-bit digit pairs (and, on request, the Karatsuba schedule and the
         # int8 level products)
         out["adaptive_width"] = extra(mode_opts(md.MDGEMM_SLICE_BITS_AUTO), 0)
-        out["karatsuba"] = extra(mode_opts(13), md.MDGEMM_KARATSUBA)
+        out["karatsuba"] = extra(mode_opts(13), md.MDGEMM_KARATSUBA | md.MDGEMM_STAGED)
         out["int8"] = int8_mode()
         if args.extras:
-            out["karatsuba_adaptive"] = extra(mode_opts(md.MDGEMM_SLICE_BITS_AUTO), md.MDGEMM_KARATSUBA)
+            out["karatsuba_adaptive"] = extra(mode_opts(md.MDGEMM_SLICE_BITS_AUTO),
+                                              md.MDGEMM_KARATSUBA | md.MDGEMM_STAGED)
     def grouped(g_flags):
         """A few timed steps of the same workload as a grouped product (section 3's
         exponent classes over the workload's range, or sign groups), with a
