@@ -1316,6 +1316,9 @@ int noalloc_impl(int64_t m, int64_t n, int64_t k, int limbs, const double* A, co
   if (m < 0 || n < 0 || k < 0) return MDGEMM_EINVAL;
   MDG_TRY(resolve(limbs, m, n, k, &o, &r));
   if (m == 0 || n == 0) return MDGEMM_OK;
+  // the array is scratch with or without the caller's flag; what fits it is decided by
+  // the size without
+  o.flags &= ~MDGEMM_WORKSPACE_SCRATCH;
   const size_t need = mdgemm_workspace_bytes(m, n, k, limbs, &o);
   if (need == SIZE_MAX) return MDGEMM_EINVAL;
   if (need > MDGEMM_NOALLOC_MAX_BYTES) return MDGEMM_EWORKSPACE;
