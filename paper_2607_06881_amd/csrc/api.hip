@@ -516,8 +516,8 @@ std::shared_ptr<const mdg::ModPlan> modular_for(int64_t m, int64_t n, int64_t k,
   if (!scratch || (r.kind != Kind::kLevels && r.kind != Kind::kKaratsuba) ||
       (r.flags & (MDGEMM_STAGED | MDGEMM_KARATSUBA_MIN_TERMS)) || r.Ge > 1 || r.sign)
     return nullptr;
-  if (mdg::accum_words(r.T + 1, r.w) > mdg::kModMaxWords || m > (int64_t{1} << 27) || n > (int64_t{1} << 27))
-    return nullptr;
+  // every limit of the launches is asked here, before anything is enqueued
+  if (mdg::accum_words(r.T + 1, r.w) > mdg::kModMaxWords || !mdg::modular_split_fits(m, n, k)) return nullptr;
   auto pl = mdg::modular_plan(m, n, k, r.S, r.T, r.w);
   if (!pl || !mdg::modular_gemm_fits(mdg::mod_kp(k), pl->pa) || !mdg::modular_gemm_fits(mdg::mod_kp(k), pl->pb))
     return nullptr;
@@ -610,7 +610,9 @@ bool levels_on_int8(int64_t m, int64_t n, int64_t k, const Resolved& r, const Pl
     return false;
   const int c = mdg::sub_digits(r.w), heaviest = max_pairs(r.S, r.T), pairs = pair_count(r.S, r.T);
   const int64_t kp = mdg::mod_kp(k), panels = int64_t{c} * r.S;
-  if (n > mdg::kLevelsMaxN || c * r.S > mdg::kModMaxBlocks || !mdg::modular_gemm_fits(kp, static_cast<int>(panels))) return false;
+  if (n > mdg::kLevelsMaxN || c * r.S > mdg::kModMaxBlocks || !mdg::modular_split_fits(m, n, k) ||
+      !mdg::modular_gemm_fits(kp, static_cast<int>(panels)))
+    return false;
   // int32 sums of products of magnitude 2^12
   if (static_cast<double>(heaviest) * c * static_cast<double>(k) >= static_cast<double>(1 << 19)) return false;
   if (static_cast<size_t>(kp * panels) * static_cast<size_t>(mdg::mod_rows(m)) > L.db - L.da ||

@@ -34,6 +34,8 @@ constexpr int kModMaxBlocks = 136;
 constexpr int kModMaxPanels = 512;
 constexpr int kModMaxGroups = 136;
 constexpr int kModMaxJobs = 320;
+constexpr int kModMaxDirect = kModMaxJobs;  // planes of the direct groups: one per direct job
+constexpr int kModMaxChannelBlocks = 96;    // the residue groups' planes by sixteens, each group's apart
 constexpr int kDirectTypes = 10;  // sub-digit products of a digit pair (4 sub-digits)
 constexpr int kModMaxBits = 192;  // integer of a residue block
 constexpr int kModTile = 256;     // output tile edge of the int8 products
@@ -98,8 +100,15 @@ constexpr int64_t kLevelsMaxN = int64_t{1} << 20;  // a tile's rows of a plane i
 inline int sub_digits(int w) { return w <= 7 ? 1 : (w + 7) / 7; }
 
 // The plan for the digit pairs p + q <= T of S digits of w bits and an m x k by
-// k x n product; nullptr when none fits the limits above (or the int32 sums).
+// k x n product; nullptr when none fits the limits above (or the int32 sums).  A plan
+// that is returned is one that the accumulation takes (modular_accum_fits): the choice
+// of the path asks nothing else about the planes after it has enqueued work.
 std::shared_ptr<const ModPlan> modular_plan(int64_t m, int64_t n, int64_t k, int S, int T, int w);
+
+// Whether the accumulation's tables hold the plan's planes (modular_accum.hip; host only).
+bool modular_accum_fits(const ModPlan& pl, int w);
+// Whether one launch of the split holds an m x k by k x n product (modular_split.hip; host only).
+bool modular_split_fits(int64_t m, int64_t n, int64_t k);
 
 constexpr int kModMaxWords = 15;  // 64-bit words of the accumulated integer
 

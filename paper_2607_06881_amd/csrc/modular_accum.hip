@@ -37,7 +37,6 @@ namespace {
 __constant__ const QuadTable kQuadTable = make_quad_table();
 
 constexpr int kElems = 2;        // elements per thread
-constexpr int kMaxBlocks = 96;   // blocks of sixteen channels
 constexpr int kDirectBatch = 6;  // direct planes loaded together
 
 // The tables are whole dwords, 4-byte aligned: scalar loads ignore the two low bits
@@ -55,7 +54,6 @@ struct Direct {
   uint32_t where;  // out | column << 16 | shift << 24
   int32_t coef;
 };
-constexpr int kMaxDirect = 264;
 struct AccumArgs {
   int64_t m, n;
   const uint32_t* P;
@@ -63,9 +61,10 @@ struct AccumArgs {
   double* C;
   int L, w, base;  // base: the grid scale of N is 2^(EA + EB - base)
   int blocks, directs, columns;  // columns: levels of the carry chain
-  Block block[kMaxBlocks];
-  Direct direct[kMaxDirect];
+  Block block[kModMaxChannelBlocks];
+  Direct direct[kModMaxDirect];
 };
+static_assert(sizeof(AccumArgs) <= 4096, "the kernel arguments of one launch");
 
 // The bytes of (a, b, c, d) for this thread's two rows: o[e] holds byte 2 half + e of
 // each; sel picks them from two dwords at a time.
@@ -237,7 +236,7 @@ void direct_coefs(int w, int64_t (&d)[kDirectTypes]) {
     }
 }
 
-// The kernel's view of a plan.
+// The kernel's view of a plan; false when its planes do not fit the tables.
 bool accum_args(const ModPlan& pl, int w, AccumArgs* a) {
   static const std::vector<std::pair<int, int>> systems = [] {
     std::vector<std::pair<int, int>> v;  // limbs and first table row of every system
@@ -267,7 +266,7 @@ bool accum_args(const ModPlan& pl, int w, AccumArgs* a) {
                            static_cast<int32_t>(c)});
     }
   }
-  if (dir.size() > static_cast<size_t>(kMaxDirect)) return false;
+  if (dir.size() > static_cast<size_t>(kModMaxDirect)) return false;
   auto column = [](const Direct& d) { return static_cast<int>((d.where >> 16) & 0xffu); };
   std::stable_sort(dir.begin(), dir.end(), [&](const Direct& x, const Direct& y) { return column(x) < column(y); });
   a->directs = static_cast<int>(dir.size());
@@ -276,7 +275,7 @@ bool accum_args(const ModPlan& pl, int w, AccumArgs* a) {
   for (const ModGroup& g : res) {
     if (g.shift != 0) return false;
     for (int i = 0; i < g.count; i += 16) {
-      if (a->blocks == kMaxBlocks) return false;
+      if (a->blocks == kModMaxChannelBlocks) return false;
       Block& d = a->block[a->blocks++];
       const uint32_t channels = static_cast<uint32_t>(std::min(16, g.count - i));
       d.where = static_cast<uint32_t>(g.out + i) | static_cast<uint32_t>(systems[g.count].second + i / 4) << 16;
@@ -289,6 +288,11 @@ bool accum_args(const ModPlan& pl, int w, AccumArgs* a) {
 }
 
 }  // namespace
+
+bool modular_accum_fits(const ModPlan& pl, int w) {
+  AccumArgs a{};
+  return accum_args(pl, w, &a);
+}
 
 hipError_t launch_modular_accum(int64_t m, int64_t n, int L, int T, int w, const ModPlan& pl, const uint32_t* P,
                                 const int32_t* EA, const int32_t* EB, double* C, hipStream_t stream) {

@@ -308,7 +308,7 @@ std::shared_ptr<const ModPlan> modular_plan(int64_t m, int64_t n, int64_t k, int
     // longest job is its time
     for (int64_t longest : {int64_t{255}, int64_t{2}}) {
       auto pl = std::make_shared<ModPlan>();
-      if (!build(rects, longest, kc, S, T, w, pl.get())) continue;
+      if (!build(rects, longest, kc, S, T, w, pl.get()) || !modular_accum_fits(*pl, w)) continue;
       pl->seconds = estimate(*pl, mc, nc, kc);
       if (!best || pl->seconds < best->seconds) best = pl;
     }

@@ -287,13 +287,10 @@ hipError_t launch_split_tile(SplitArgs& a, hipStream_t stream) {
   if (NW >= 8) lds = std::max(lds, sizeof(uint4) * (2 * NW + 1) * 4 * TK);
   int64_t gx = 0;
   for (SplitOperand& op : a.op) {
-    const int64_t tiles = (op.lines + kLines - 1) / kLines;
-    if (tiles > (1 << 30)) return hipErrorInvalidValue;
-    op.tiles = static_cast<int>(tiles);
-    gx += tiles;
+    op.tiles = static_cast<int>((op.lines + kLines - 1) / kLines);
+    gx += op.tiles;
   }
   const int64_t gy = (a.kp + TK - 1) / TK;
-  if (gy > 65535 || gx > 0x7fffffff) return hipErrorInvalidValue;
   const int64_t gz = std::min<int64_t>(8, std::max<int64_t>(1, 512 / (gx * gy)));
   auto kernel = modular_split_kernel<NW, ML, TK, kWin>;
   if (lds > 64 * 1024) {
@@ -308,12 +305,21 @@ hipError_t launch_split_tile(SplitArgs& a, hipStream_t stream) {
 
 }  // namespace
 
+// Grid limits of the tiles above, whichever is taken: below 2^32 threads along x (blocks
+// of up to 512 threads per 16 lines) and 65535 blocks along y (64 values of k at least).
+bool modular_split_fits(int64_t m, int64_t n, int64_t k) {
+  if (m > (int64_t{1} << 30) || n > (int64_t{1} << 30)) return false;
+  const int64_t tiles = (m + kLines - 1) / kLines + (n + kLines - 1) / kLines;
+  return tiles * 512 < (int64_t{1} << 32) && (mod_kp(k) + 63) / 64 <= 65535;
+}
+
 hipError_t launch_modular_split(int64_t m, int64_t n, int64_t k, int L, int S, int w, const double* A,
                                 const double* B, const int32_t* EA, const int32_t* EB, int8_t* DA, int8_t* DB,
                                 const std::vector<ModBlock>& ba, int pa, const std::vector<ModBlock>& bb, int pb,
                                 hipStream_t stream) {
   if (m == 0 || n == 0 || k == 0) return hipSuccess;
-  if (ba.size() > static_cast<size_t>(kModMaxBlocks) || bb.size() > static_cast<size_t>(kModMaxBlocks))
+  if (ba.size() > static_cast<size_t>(kModMaxBlocks) || bb.size() > static_cast<size_t>(kModMaxBlocks) ||
+      !modular_split_fits(m, n, k))
     return hipErrorInvalidValue;
   SplitArgs a{};
   a.K = k;

@@ -64,6 +64,16 @@ CASES = [
     (2, 300, 300, 200, {"cutoff": 3}),
     (2, 70, 4000, 300, {}),
     (2, 4100, 40, 300, {}),
+    # a level's pairs split into several sums, more than 264 planes, two GEMM launches
+    (16, 300, 300, 1500, {}),
+    (8, 300, 300, 4096, {"cutoff": ALL}),
+    (8, 300, 300, 7000, {}),
+    (4, 258, 260, 16384, {"slice_bits": -1}),
+    (2, 300, 300, 5000, {"slice_bits": -1, "range_bits": 60}),
+    (11, 300, 270, 20, {"slice_bits": -1}),
+    # the longest sums of residues and of sub-digits
+    (2, 260, 270, 32768, {}),
+    (2, 257, 300, 65536, {"slice_bits": 8}),
 ]
 
 

@@ -1,0 +1,198 @@
+"""Plans of the int8 products (CPU only): what the library chooses can be run, and is the product.
+
+The library takes a plan when the workspace sizes with and without MDGEMM_WORKSPACE_SCRATCH
+differ.  Every such plan must fit the tables and sums of the kernels that run it, and, evaluated in
+Python integers on a few elements, give the sum of the kept digit pairs exactly.
+"""
+
+import ctypes
+import os
+import random
+import subprocess
+
+import pytest
+
+from paper_2607_06881_amd import mdgemm as md
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2607_06881_amd", "csrc")
+ALL, AUTO = md.MDGEMM_CUTOFF_ALL, md.MDGEMM_SLICE_BITS_AUTO
+DIRECT = 255  # a job's `mod` when its sums are stored as they are
+
+
+@pytest.fixture(scope="module")
+def probe(tmp_path_factory):
+    if not os.path.exists(md.LIB_PATH):
+        import __graft_entry__
+
+        __graft_entry__.build()
+    md.lib()
+    so = str(tmp_path_factory.mktemp("probe") / "plan_probe.so")
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, "-o", so, os.path.join(HERE, "plan_probe.cpp"),
+                    md.LIB_PATH], check=True)
+    p = ctypes.CDLL(so)
+    p.probe_plan.restype = ctypes.c_int64
+    p.probe_plan.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 3 + [ctypes.c_void_p, ctypes.c_int64]
+    p.probe_split_fits.argtypes = [ctypes.c_int64] * 3
+    return p
+
+
+def _plan(probe, m, n, k, S, T, w):
+    buf = (ctypes.c_int64 * 20000)()
+    count = probe.probe_plan(m, n, k, S, T, w, buf, len(buf))
+    if count < 0:
+        return None
+    assert count <= len(buf)
+    v = iter(buf[:count])
+    take = lambda rows, width: [tuple(next(v) for _ in range(width)) for _ in range(rows)]  # noqa: E731
+    na, nb, nj, ng, pa, pb, planes, fits = (next(v) for _ in range(8))
+    return {"a": take(na, 5), "b": take(nb, 5), "jobs": take(nj, 7), "groups": take(ng, 4), "pa": pa, "pb": pb,
+            "planes": planes, "fits": bool(fits)}
+
+
+def _options():
+    yield "default", {}
+    yield "every pair", {"cutoff": ALL}
+    yield "adaptive", {"slice_bits": AUTO}
+    yield "adaptive, every pair", {"slice_bits": AUTO, "cutoff": ALL}
+    yield "int8", {"flags": md.MDGEMM_INT8}
+    for bits in (24, 60):
+        yield f"range {bits}", {"range_bits": bits}
+        yield f"range {bits}, adaptive", {"range_bits": bits, "slice_bits": AUTO}
+    for w in (4, 7, 8, 16, 21, 26):
+        yield f"{w} bits", {"slice_bits": w}
+
+
+def _chosen(m, n, k, L, opts):
+    """(w, S, T) when the library would run int8 products, else None."""
+    opts = dict(opts)
+    flags = opts.pop("flags", 0)
+    try:
+        plan = md.mdgemm_plan(m, n, k, L, flags=flags, **opts)
+    except md.MdgemmError:
+        return None
+    if (md.mdgemm_workspace_bytes(m, n, k, L, flags=flags | md.MDGEMM_WORKSPACE_SCRATCH, **opts)
+            == md.mdgemm_workspace_bytes(m, n, k, L, flags=flags, **opts)):
+        return None
+    return plan
+
+
+@pytest.mark.parametrize("name,opts", list(_options()))
+def test_a_chosen_plan_fits_the_kernels(probe, name, opts):
+    seen = 0
+    for L in range(1, 17):
+        for k in sorted({int(2 ** (x / 2)) for x in range(33)} | {1500, 3000, 6000}):
+            for m, n in ((300, 300), (2048, 2048), (70, 4000)):
+                plan = _chosen(m, n, k, L, opts)
+                if plan is None:
+                    continue
+                w, S, T = plan
+                pl = _plan(probe, m, n, k, S, T, w)
+                seen += 1
+                what = (name, L, m, n, k, w, S, T)
+                assert pl is not None and pl["fits"], what
+                assert all(shift == 0 for shift, _, residue, _ in pl["groups"] if residue), what
+                # operands at most 128 in magnitude: residue sums up to 2^29, int32 sums up to 2^30
+                for *_, nseg, mod, _ in pl["jobs"]:
+                    assert nseg * k * 2 ** 14 <= (2 ** 30 if mod == DIRECT else 2 ** 29), what
+                assert 256 * max(pl["pa"], pl["pb"]) * ((k + 127) // 128 * 128) < 2 ** 31, what
+    assert seen
+
+
+def _balanced(v, m):
+    v %= m
+    return v - m if 2 * v > m else v
+
+
+def _sub_digits(d, c):
+    out = []
+    for _ in range(c - 1):
+        s = (d + 64) % 128 - 64
+        out.append(s)
+        d = (d - s) // 128
+    out.append(d)
+    return out
+
+
+def _panels(blocks, moduli, D, sign):
+    """The int8 panels of one element with digits D (a natural number) and a sign."""
+    out = []
+    for lo, bits, count, residue, scaled in blocks:
+        e = (D >> lo) & ((1 << bits) - 1)
+        if residue:
+            M = 1
+            for m in moduli[:count]:
+                M *= m
+            for m in moduli[:count]:
+                f = pow(M // m, -1, m) if scaled else 1
+                out.append(sign * _balanced(e * f, m))
+        else:
+            c = {1: 1, 3: 2, 6: 3, 10: 4}[count]
+            s = _sub_digits(sign * e, c)
+            out += s + [s[i] + s[j] for i in range(c) for j in range(i + 1, c)]
+    assert all(-128 <= x <= 128 for x in out)
+    return out
+
+
+def _value(pl, moduli, A, B, w):
+    """The accumulated integer of sum over A[x] B[x], each (digits, sign)."""
+    pa = [_panels(pl["a"], moduli, *x) for x in A]
+    pb = [_panels(pl["b"], moduli, *x) for x in B]
+    planes = {}
+    for a, b, da, db, nseg, mod, out in pl["jobs"]:
+        s = sum(x[a + i * da] * y[b + i * db] for x, y in zip(pa, pb) for i in range(nseg))
+        assert out not in planes
+        planes[out] = s if mod == DIRECT else s % moduli[mod]
+    total = 0
+    for shift, out, residue, count in pl["groups"]:
+        if residue:
+            M = 1
+            for m in moduli[:count]:
+                M *= m
+            V = _balanced(sum(planes[out + i] * (M // moduli[i]) for i in range(count)), M)
+        else:
+            c = {1: 1, 3: 2, 6: 3, 10: 4}[count]
+            x = [planes[out + 4 * i] for i in range(count)]
+            V, nxt = sum(x[i] << (14 * i) for i in range(c)), c
+            for i in range(c):
+                for j in range(i + 1, c):
+                    V += (x[nxt] - x[i] - x[j]) << (7 * (i + j))
+                    nxt += 1
+        total += V << shift
+    return total
+
+
+@pytest.mark.parametrize("m,n,k,S,T,w", [
+    (4096, 4096, 4096, 8, 7, 13), (300, 300, 700, 8, 14, 13), (2048, 2048, 1024, 16, 15, 13), (500, 500, 40, 34, 33, 13),
+    (300, 300, 1500, 66, 65, 13), (300, 300, 7000, 34, 33, 13), (300, 300, 3000, 34, 66, 13), (300, 300, 16384, 11, 10, 20),
+    (128, 8192, 64, 66, 65, 13), (900, 900, 30000, 15, 14, 7), (400, 400, 300, 3, 2, 26), (400, 400, 300, 5, 8, 21),
+    (200, 200, 2000, 20, 3, 5), (300, 300, 32768, 4, 3, 13), (300, 300, 50000, 13, 12, 8), (300, 300, 9, 1, 0, 13),
+    (300, 300, 200, 36, 40, 16), (300, 300, 200, 12, 20, 9),
+])
+def test_a_plan_forms_the_sum_of_the_kept_pairs(probe, m, n, k, S, T, w):
+    pl = _plan(probe, m, n, k, S, T, w)
+    assert pl is not None and pl["fits"]
+    moduli = [probe.probe_modulus(i) for i in range(40)]
+    rng = random.Random(S * 1000 + T)
+    top = (1 << (w * S)) - 1
+    for terms in (1, 5):
+        # random digits, and the largest of either sign
+        for draw in (lambda: (rng.getrandbits(w * S), rng.choice((-1, 1))), lambda: (top, rng.choice((-1, 1)))):
+            A, B = [draw() for _ in range(terms)], [draw() for _ in range(terms)]
+            want = 0
+            for (x, sx), (y, sy) in zip(A, B):
+                dx = [(x >> (w * (S - 1 - p))) & ((1 << w) - 1) for p in range(S)]
+                dy = [(y >> (w * (S - 1 - p))) & ((1 << w) - 1) for p in range(S)]
+                want += sx * sy * sum(dx[p] * dy[q] << (w * (T - p - q))
+                                      for p in range(S) for q in range(S) if p + q <= T)
+            # the residues of a group recover |V| < M / 2 only for the sums of at most k terms
+            if terms <= k:
+                assert _value(pl, moduli, A, B, w) == want
+
+
+def test_lines_beyond_one_launch_of_the_split_are_refused(probe):
+    """gridDim.x blockDim.x below 2^32: 16 lines per block of up to 512 threads."""
+    assert probe.probe_split_fits(1 << 26, 1 << 25, 4096)
+    assert not probe.probe_split_fits(1 << 27, 1, 1)
+    assert not probe.probe_split_fits((1 << 27) - 16, 1, 1)
+    assert _chosen(1 << 27, 1, 1, 1, {}) is None
