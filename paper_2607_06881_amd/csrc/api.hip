@@ -613,8 +613,7 @@ bool levels_on_int8(int64_t m, int64_t n, int64_t k, const Resolved& r, const Pl
   if (n > mdg::kLevelsMaxN || c * r.S > mdg::kModMaxBlocks || !mdg::modular_split_fits(m, n, k) ||
       !mdg::modular_gemm_fits(kp, static_cast<int>(panels)))
     return false;
-  // int32 sums of products of magnitude 2^12
-  if (static_cast<double>(heaviest) * c * static_cast<double>(k) >= static_cast<double>(1 << 19)) return false;
+  if (!mdg::level_passes_exact(heaviest, k, r.w)) return false;
   if (static_cast<size_t>(kp * panels) * static_cast<size_t>(mdg::mod_rows(m)) > L.db - L.da ||
       static_cast<size_t>(kp * panels) * static_cast<size_t>(mdg::mod_rows(n)) > L.g - L.db)
     return false;

@@ -98,6 +98,14 @@ LevelPlan level_plan(int S, int T, int w);
 constexpr int64_t kLevelsMaxN = int64_t{1} << 20;  // a tile's rows of a plane in 32-bit offsets
 // 7-bit sub-digits of a w-bit digit (balanced, the last one up to 64 in magnitude).
 inline int sub_digits(int w) { return w <= 7 ? 1 : (w + 7) / 7; }
+// Whether the int32 sums of a pass hold for levels of up to `pairs` pairs: up to c runs of
+// k products per pair.  A digit of at most 7 bits is its own sub-digit, up to 2^w - 1 in
+// magnitude (products below 2^14); wider ones give balanced sub-digits of at most 64.
+inline bool level_passes_exact(int pairs, int64_t k, int w) {
+  const int64_t d = w <= 7 ? (int64_t{1} << w) - 1 : 64;
+  return static_cast<double>(pairs) * sub_digits(w) * static_cast<double>(k) * static_cast<double>(d * d) <
+         2147483648.0;
+}
 
 // The plan for the digit pairs p + q <= T of S digits of w bits and an m x k by
 // k x n product; nullptr when none fits the limits above (or the int32 sums).  A plan

@@ -36,4 +36,5 @@ extern "C" int64_t probe_plan(int64_t m, int64_t n, int64_t k, int S, int T, int
 }
 
 extern "C" int probe_modulus(int i) { return mdg::kModuli[i]; }
+extern "C" int probe_level_passes_exact(int pairs, int64_t k, int w) { return mdg::level_passes_exact(pairs, k, w); }
 extern "C" int probe_split_fits(int64_t m, int64_t n, int64_t k) { return mdg::modular_split_fits(m, n, k); }

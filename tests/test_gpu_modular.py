@@ -184,6 +184,26 @@ def test_a_readable_workspace_holds_digits_and_levels(L, m, n, k, opts):
     assert not torch.signbit(parts[0]["G"][parts[0]["G"] == 0]).any().item()
 
 
+@pytest.mark.parametrize("m,n,k,opts", [
+    # 7-bit digits are not split: 15 pairs of 127^2 each pass 2^31 between these two k
+    (1024, 1024, 8876, {"slice_bits": 7}), (1024, 1024, 8877, {"slice_bits": 7}),
+    (1024, 1024, 9000, {"slice_bits": 7}), (1024, 1024, 24000, {"slice_bits": 6}),
+])
+def test_levels_of_the_largest_digits_in_a_readable_workspace(m, n, k, opts):
+    print(f"[case] largest digits, readable workspace {m}x{n}x{k} {opts}", flush=True)
+    A = torch.full((2, m, k), 1.0 - 2.0 ** -53, dtype=torch.float64, device=DEV)
+    B = torch.full((2, k, n), 1.0 - 2.0 ** -53, dtype=torch.float64, device=DEV)
+    A[1], B[1] = 2.0 ** -54 * (1.0 - 2.0 ** -53), 2.0 ** -54 * (1.0 - 2.0 ** -53)
+    A[:, ::2] *= -1.0
+    need = md.mdgemm_workspace_bytes(m, n, k, 2, **opts)
+    ws = [torch.empty(need, dtype=torch.uint8, device=DEV) for _ in range(2)]
+    got = md.mdgemm_ex(A, B, workspace=ws[0], **opts)
+    want = md.mdgemm_ex(A, B, workspace=ws[1], flags=md.MDGEMM_STAGED, **opts)
+    assert torch.equal(got, want)
+    parts = [md.workspace_parts(w, m, n, k, 2, flags=f, **opts) for w, f in zip(ws, (0, md.MDGEMM_STAGED))]
+    assert torch.equal(parts[0]["G"], parts[1]["G"])
+
+
 def _least(total, shapes):
     """A QR's or Taylor series' workspace without room for the int8 products: the size with
     its part for the products (the largest need of `shapes`) replaced."""

@@ -34,6 +34,7 @@ def probe(tmp_path_factory):
     p.probe_plan.restype = ctypes.c_int64
     p.probe_plan.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 3 + [ctypes.c_void_p, ctypes.c_int64]
     p.probe_split_fits.argtypes = [ctypes.c_int64] * 3
+    p.probe_level_passes_exact.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int]
     return p
 
 
@@ -196,3 +197,18 @@ def test_lines_beyond_one_launch_of_the_split_are_refused(probe):
     assert not probe.probe_split_fits(1 << 27, 1, 1)
     assert not probe.probe_split_fits((1 << 27) - 16, 1, 1)
     assert _chosen(1 << 27, 1, 1, 1, {}) is None
+
+
+@pytest.mark.parametrize("w", range(1, 27))
+def test_level_passes_stay_below_2_31(probe, w):
+    """A pass sums the products of c pairs of sub-digits of every digit pair of a level in int32;
+    the bound takes the largest sub-digits that digits of this width have."""
+    c = 1 if w <= 7 else (w + 7) // 7
+    top = (1 << w) - 1
+    digits = range(-top, top + 1) if w <= 14 else [s * (top - x) for x in range(1 << 14) for s in (-1, 1)]
+    largest = max(max(map(abs, _sub_digits(d, c))) for d in digits)
+    assert largest == (top if w <= 7 else 64)
+    for pairs in (1, 8, 15, 66):
+        last = (2 ** 31 - 1) // (pairs * c * largest ** 2)  # k of the largest sum below 2^31
+        assert probe.probe_level_passes_exact(pairs, last, w)
+        assert not probe.probe_level_passes_exact(pairs, last + 1, w)
