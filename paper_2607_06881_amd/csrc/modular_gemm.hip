@@ -288,6 +288,10 @@ __global__ void __launch_bounds__(512, 1) modular_gemm_kernel(int64_t m, int64_t
   }
 }
 
+// An offset beyond every plane's buffer (at most 2^31 bytes, kLevelsMaxN), also with a
+// column step added.  The steps go into the offset that the hardware checks, not into the
+// scalar one: the check is against the size minus the scalar offset, which is below zero
+// for a last tile of fewer than 48 elements (say 1 row, 1 column).
 constexpr uint32_t kOutside = 0xfffff000u;
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 
@@ -346,7 +350,7 @@ __global__ void __launch_bounds__(512, 1) modular_levels_kernel(int64_t m, int64
         for (int r = 0; r < 4; ++r)
 #pragma unroll
           for (int y = 0; y < 4; ++y)
-            old[r][y] = __builtin_amdgcn_raw_buffer_load_b64(rg, y < cols ? off + r * pitch : kOutside, 128 * y, 0);
+            old[r][y] = __builtin_amdgcn_raw_buffer_load_b64(rg, (y < cols ? off + r * pitch : kOutside) + 128 * y, 0, 0);
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r)
@@ -356,7 +360,7 @@ __global__ void __launch_bounds__(512, 1) modular_levels_kernel(int64_t m, int64
           if (s > 0) v += static_cast<int64_t>(old[r][y][0] | static_cast<uint64_t>(old[r][y][1]) << 32);
           if (last) v = __double_as_longlong(static_cast<double>(v));  // below 2^53: exact
           const v2u d = {static_cast<uint32_t>(v), static_cast<uint32_t>(v >> 32)};
-          __builtin_amdgcn_raw_buffer_store_b64(d, rg, y < cols ? off + r * pitch : kOutside, 128 * y, 0);
+          __builtin_amdgcn_raw_buffer_store_b64(d, rg, (y < cols ? off + r * pitch : kOutside) + 128 * y, 0, 0);
         }
       off += 16 * pitch;
       __builtin_amdgcn_sched_barrier(0);

@@ -34,7 +34,8 @@ def _operands(L, m, n, k, seed, spread=0):
     A = workloads.make_operand(rng, L, m, k, "normal", row_exp=20, elem_exp=spread)
     B = workloads.make_operand(rng, L, k, n, "normal", col_exp=20, elem_exp=spread)
     A[:, 0, :] = 0.0  # an all-zero line of each operand, and single zeros
-    B[:, :, n - 1] = 0.0
+    if n > 1:
+        B[:, :, n - 1] = 0.0
     A[:, m - 1, k // 2] = 0.0
     return torch.from_numpy(A).to(DEV), torch.from_numpy(B).to(DEV)
 
@@ -163,6 +164,9 @@ def test_library_buffer_capture_and_a_small_workspace():
     (2, 1283, 1409, 130, {}), (2, 1100, 900, 257, {"cutoff": ALL}), (3, 1025, 1023, 127, {}),
     (2, 1409, 1283, 300, {"slice_bits": 20}), (2, 1409, 1500, 200, {"slice_bits": 21}),
     (2, 1283, 1300, 200, {"slice_bits": 7}), (8, 520, 700, 100, {}), (2, 900, 1000, 200, {"range_bits": 60}),
+    # a last tile of few elements: one to three rows of 1 to 40 columns
+    (1, 4097, 1, 256, {}), (1, 4097, 17, 256, {}), (1, 4098, 9, 256, {}), (1, 4099, 40, 256, {}),
+    (2, 4097, 33, 384, {}),
 ])
 def test_a_readable_workspace_holds_digits_and_levels(L, m, n, k, opts):
     """Without MDGEMM_WORKSPACE_SCRATCH the workspace holds the exponents, digit panels and
