@@ -301,8 +301,9 @@ int mdgemm_ex_noalloc(int64_t m, int64_t n, int64_t k, int limbs, const double* 
                       const mdgemm_opts* opts);
 
 /* Milliseconds spent in each stage of the last mdgemm_ex call that set
- * MDGEMM_TIME_STAGES on this process: ms[0] exponents, ms[1] splits,
- * ms[2] level GEMMs, ms[3] accumulation and rounding.  Waits for that call's
+ * MDGEMM_TIME_STAGES on this process: ms[0] exponents, ms[1] splits (of the
+ * digits that a readable workspace is left with, too, where these are written
+ * last), ms[2] level GEMMs, ms[3] accumulation and rounding.  Waits for that call's
  * last event.  Writes min(count, 4) values and returns how many, or a negative
  * status.  Not meant for concurrent timed calls from several threads. */
 int mdgemm_stage_times(float* ms, int count);

@@ -208,6 +208,28 @@ def test_levels_of_the_largest_digits_in_a_readable_workspace(m, n, k, opts):
     assert torch.equal(parts[0]["G"], parts[1]["G"])
 
 
+def test_stage_times_of_levels_on_int8():
+    """The digits that the workspace is left with are split after the accumulation, and count as
+    split: the accumulation's own time is that of the FP64 levels' call (the same kernel and planes;
+    with the two splits in it, it would be more than four times as long)."""
+    m, n, k, opts = 1100, 900, 4096, {"cutoff": ALL}
+    print(f"[case] stage times, readable workspace {m}x{n}x{k}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(3)
+    A, B = (torch.randn(2, *shape, dtype=torch.float64, device=DEV, generator=g) for shape in ((m, k), (k, n)))
+    A[1], B[1] = A[0] * 2.0 ** -55, B[0] * 2.0 ** -55
+    ws = torch.empty(md.mdgemm_workspace_bytes(m, n, k, 2, **opts), dtype=torch.uint8, device=DEV)
+    times = {}
+    for flags in (md.MDGEMM_STAGED, 0):
+        calls = []
+        for _ in range(4):
+            md.mdgemm_ex(A, B, workspace=ws, flags=flags | md.MDGEMM_TIME_STAGES, **opts)
+            calls.append(md.mdgemm_stage_times())
+        times[flags] = np.min(calls, axis=0)
+    staged, int8 = times[md.MDGEMM_STAGED], times[0]
+    assert int8[2] < 0.5 * staged[2]  # the levels did run on the int8 matrix cores
+    assert int8[3] < 2.0 * staged[3] and int8[1] > staged[1], times
+
+
 def _least(total, shapes):
     """A QR's or Taylor series' workspace without room for the int8 products: the size with
     its part for the products (the largest need of `shapes`) replaced."""
