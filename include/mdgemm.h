@@ -199,7 +199,8 @@ typedef struct mdgemm_opts {
  * with one int8 product per modulus and recovered by the Chinese remainder theorem,
  * or, for single pairs, by Karatsuba's identity on 7-bit sub-digits: every limb
  * equals that of the FP64 level products.  MDGEMM_INT8 chooses the digits; their
- * products run this way too where the workspace has room and it is estimated faster.
+ * products run this way too where nothing reads the workspace and it is estimated
+ * faster.
  * Not with MDGEMM_STAGED, MDGEMM_KARATSUBA_MIN_TERMS or the grouped products, nor for
  * k above 2^15.
  * In a workspace that may be read, the pair schedule's levels are formed one by one

@@ -1061,27 +1061,19 @@ int ex_impl(int64_t m, int64_t n, int64_t k, int limbs, const double* A, const d
     return MDGEMM_OK;
   }
 
-  // the int8 products, when the workspace is scratch (always with MDGEMM_INT8, whose
-  // workspace no call describes) and holds them; else the paths below, in the
-  // workspace they always took
+  // the int8 products, when the workspace is scratch and holds them; else the paths
+  // below, in the workspace they always took.  A caller workspace that is not marked
+  // scratch keeps its described contents, with MDGEMM_INT8 too.
   const bool caller_ws = opts && opts->workspace;
-  const auto mod = modular_for(m, n, k, limbs, r,
-                               !caller_ws || (r.flags & (MDGEMM_WORKSPACE_SCRATCH | MDGEMM_INT8)));
+  const auto mod = modular_for(m, n, k, limbs, r, !caller_ws || (r.flags & MDGEMM_WORKSPACE_SCRATCH));
   LayoutMod lm;
-  size_t taken = 0;  // of the caller workspace: what the other path would check as well
-  if (caller_ws && (r.flags & MDGEMM_INT8) && !(r.flags & MDGEMM_WORKSPACE_SCRATCH)) {
-    LayoutI8 l8;
-    if (!layout_int8(m, n, k, r.S, r.T, &l8)) return MDGEMM_EINVAL;
-    if (opts->workspace_bytes < l8.total) return MDGEMM_EWORKSPACE;
-    taken = l8.total;
-  }
   if (mod && layout_modular(m, n, k, *mod, &lm) && (!caller_ws || opts->workspace_bytes >= lm.total)) {
     *path = "int8 residues";
     char* ws = nullptr;
     LibraryBuffer lib;
     int st = MDGEMM_OK;
     if (caller_ws) {
-      if (workspace_overlaps(opts->workspace, std::max(lm.total, taken), m, n, k, limbs, A, B, C)) return MDGEMM_EINVAL;
+      if (workspace_overlaps(opts->workspace, lm.total, m, n, k, limbs, A, B, C)) return MDGEMM_EINVAL;
       ws = static_cast<char*>(opts->workspace);
     } else {
       st = lib.acquire(lm.total, s, &ws);

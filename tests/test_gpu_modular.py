@@ -208,6 +208,41 @@ def test_levels_of_the_largest_digits_in_a_readable_workspace(m, n, k, opts):
     assert torch.equal(parts[0]["G"], parts[1]["G"])
 
 
+@pytest.mark.parametrize("L,m,n,k,opts", [(2, 700, 650, 300, {}), (3, 513, 600, 200, {"slice_bits": 5})])
+def test_a_readable_int8_workspace_holds_digits_and_levels(L, m, n, k, opts):
+    """The parts that the header lists for MDGEMM_INT8, at the sizes where products in scratch run
+    otherwise: exponents, A's digits and the int32 levels equal the FP64 path's at those digits."""
+    print(f"[case] readable int8 workspace L={L} {m}x{n}x{k} {opts}", flush=True)
+    int8 = md.MDGEMM_INT8
+    assert _modular(m, n, k, L, flags=int8, **opts)
+    A, B = _operands(L, m, n, k, 9 * m, spread=4)
+    w, S, T = md.mdgemm_plan(m, n, k, L, flags=int8, **opts)
+    need = md.mdgemm_workspace_bytes(m, n, k, L, flags=int8, **opts)
+    ws = torch.full((3 * need,), 0x5a, dtype=torch.uint8, device=DEV)  # room for any path
+    got = md.mdgemm_ex(A, B, workspace=ws, flags=int8, **opts)
+    digits = dict(slice_bits=w, slices=S, cutoff=T, flags=md.MDGEMM_STAGED)
+    staged = torch.empty(md.mdgemm_workspace_bytes(m, n, k, L, **digits), dtype=torch.uint8, device=DEV)
+    assert torch.equal(got, md.mdgemm_ex(A, B, workspace=staged, **digits))
+    want = md.workspace_parts(staged, m, n, k, L, **digits)
+    up = lambda x, to: (x + to - 1) // to * to  # noqa: E731
+    kp, mp, np_ = up(k, 128), up(m, 256), up(n, 256)
+    pitch, off, parts = 128 + S * kp, 0, {}
+    for name, size in (("EA", 4 * m), ("EB", 4 * n), ("flag", 4), ("DA", mp * pitch), ("DB", np_ * pitch),
+                       ("G", 4 * (T + 1) * m * n)):
+        parts[name] = ws[off:off + size]
+        off += up(size, 256)
+    assert off == need and (ws[need:] == 0x5a).all()
+    assert torch.equal(parts["EA"].view(torch.int32), want["EA"]) and torch.equal(parts["EB"].view(torch.int32), want["EB"])
+    da = parts["DA"].view(torch.int8).view(mp, pitch)[:m, 128:].reshape(m, S, kp)[:, :, :k]
+    assert torch.equal(da.to(torch.float32), want["DA"][:S, :k, :m].to(torch.float32).permute(2, 0, 1))
+    levels = parts["G"].view(torch.int32).view(T + 1, m, n)
+    assert md.mdgemm_workspace_layout(m, n, k, L, **digits)["direct_levels"]
+    assert torch.equal(levels.to(torch.float64), want["G"])
+    # the program may keep other data in the part of its buffer that the call does not need
+    C = ws[need:need + 8 * got.numel()].view(torch.float64).view(got.shape)
+    assert torch.equal(md.mdgemm_ex(A, B, C, workspace=ws, flags=int8, **opts), got)
+
+
 def test_stage_times_of_levels_on_int8():
     """The digits that the workspace is left with are split after the accumulation, and count as
     split: the accumulation's own time is that of the FP64 levels' call (the same kernel and planes;
