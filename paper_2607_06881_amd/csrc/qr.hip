@@ -95,10 +95,13 @@ static_assert(kPanelRowsShort <= 64 && kPanelRowsTall <= 64, "one row per thread
 // FP64 operations), on one wave per SIMD.  Three things shorten it without touching
 // any sum's order: the late steps of a panel, with at most 32 columns left, take one
 // column group (kH = 1) and skip the other's sums, which every block repeats in full;
-// loads take clamped addresses and a select instead of branches, the next batch of
-// partials on its way while one is added; and tau is formed beside v and w instead of
-// before them.  A step of 8 (16) rows took 7.3 (9.0) us, now 7.5 (9.3) with two column
-// groups and 6.4 (7.2) with one; a 2048 x 2048 factorization 28.1 ms, now 27.0.
+// the matrix's loads take clamped addresses and a select instead of branches, and with
+// one column group the partials' too, the next batch on its way while one is added
+// (with two, the registers of a second batch cost more than its wait: 7.6 us a step
+// against 6.9 at 8 rows, 9.4 against 8.7 at 16, 10.6 against 10.1 at 32); and tau is
+// formed beside v and w instead of before them.  The first 33 steps of a panel of 8, 16
+// or 32 rows a block took 7.4, 9.4 and 11.2 us in the form before and take 6.9, 8.7 and
+// 10.1, the other 32 took 7.0, 8.7 and 9.7 us and take 6.5, 7.4 and 8.0.
 template <int kRows, int kH>
 __global__ void __launch_bounds__(kColThreads) qr_col_step_kernel(int64_t m, int64_t n, int64_t j0, int jb, int s,
                                                                   double* __restrict__ A, double* __restrict__ tau,
@@ -155,24 +158,34 @@ __global__ void __launch_bounds__(kColThreads) qr_col_step_kernel(int64_t m, int
 #pragma unroll
       for (int h = 0; h < kH; ++h) sum[h] = {0.0, 0.0};
       constexpr int64_t kBatch = kRowGroups * kFoldBatch;
-      dd v[kH][kFoldBatch], next[kH][kFoldBatch];
-      auto load = [&](dd(&x)[kH][kFoldBatch], int64_t b0) {
+      if constexpr (kH == 2) {
+        for (int64_t b0 = rg; b0 < G; b0 += kBatch) {
+          dd v[kH][kFoldBatch];
 #pragma unroll
-        for (int h = 0; h < kH; ++h)
+          for (int h = 0; h < kH; ++h)
 #pragma unroll
-          for (int u = 0; u < kFoldBatch; ++u) x[h][u] = ldd(pd_in, pplane, min(b0 + kRowGroups * u, G - 1) * kMaxNb + 32 * h + cc);
-      };
-      load(v, rg);
-      for (int64_t b0 = rg; b0 < G; b0 += kBatch) {
-        if (b0 + kBatch < G) load(next, b0 + kBatch);
+            for (int u = 0; u < kFoldBatch; ++u) {
+              const int64_t b = b0 + kRowGroups * u;
+              v[h][u] = b < G && 32 * h + cc < ncols ? ldd(pd_in, pplane, b * kMaxNb + 32 * h + cc) : dd{0.0, 0.0};
+            }
 #pragma unroll
-        for (int h = 0; h < kH; ++h) {
+          for (int h = 0; h < kH; ++h) sum[h] = dd_add(sum[h], tree_sum<kFoldBatch>(v[h]));
+        }
+      } else {
+        dd v[kFoldBatch], next[kFoldBatch];
+        auto load = [&](dd(&x)[kFoldBatch], int64_t b0) {
+#pragma unroll
+          for (int u = 0; u < kFoldBatch; ++u) x[u] = ldd(pd_in, pplane, min(b0 + kRowGroups * u, G - 1) * kMaxNb + cc);
+        };
+        load(v, rg);
+        for (int64_t b0 = rg; b0 < G; b0 += kBatch) {
+          if (b0 + kBatch < G) load(next, b0 + kBatch);
 #pragma unroll
           for (int u = 0; u < kFoldBatch; ++u)
-            if (b0 + kRowGroups * u >= G || 32 * h + cc >= ncols) v[h][u] = dd{0.0, 0.0};
-          sum[h] = dd_add(sum[h], tree_sum<kFoldBatch>(v[h]));
+            if (b0 + kRowGroups * u >= G || cc >= ncols) v[u] = dd{0.0, 0.0};
+          sum[0] = dd_add(sum[0], tree_sum<kFoldBatch>(v));
 #pragma unroll
-          for (int u = 0; u < kFoldBatch; ++u) v[h][u] = next[h][u];
+          for (int u = 0; u < kFoldBatch; ++u) v[u] = next[u];
         }
       }
 #pragma unroll
