@@ -296,12 +296,22 @@ def mdgemm_ex(A: torch.Tensor, B: torch.Tensor, C: Optional[torch.Tensor] = None
         if tuple(C.shape) != (L, m, n):
             raise ValueError("C has the wrong shape")
     if workspace is None:
-        flags |= MDGEMM_WORKSPACE_SCRATCH
-        need = mdgemm_workspace_bytes(m, n, k, L, slices_per_limb=slices_per_limb, cutoff=cutoff,
-                                      slice_bits=slice_bits, slices=slices, range_bits=range_bits, flags=flags)
-        if need == 2**64 - 1:
-            _check(MDGEMM_EINVAL, "mdgemm_workspace_bytes")
-        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=A.device)
+        def need(flags):
+            size = mdgemm_workspace_bytes(m, n, k, L, slices_per_limb=slices_per_limb, cutoff=cutoff,
+                                          slice_bits=slice_bits, slices=slices, range_bits=range_bits, flags=flags)
+            if size == 2**64 - 1:
+                _check(MDGEMM_EINVAL, "mdgemm_workspace_bytes")
+            return max(size, 1)
+
+        plain, flags = flags & ~MDGEMM_WORKSPACE_SCRATCH, flags | MDGEMM_WORKSPACE_SCRATCH
+        try:
+            workspace = torch.empty(need(flags), dtype=torch.uint8, device=A.device)
+        except torch.OutOfMemoryError:
+            # the int8 products' panels can take several times the room of the FP64 ones, which
+            # are enough
+            if need(plain) >= need(flags):
+                raise
+            workspace = torch.empty(need(plain), dtype=torch.uint8, device=A.device)
     o = make_opts(slices_per_limb=slices_per_limb, cutoff=cutoff, flags=flags, stream=stream, workspace=workspace,
                   slice_bits=slice_bits, slices=slices, range_bits=range_bits)
     _check(lib().mdgemm_ex(m, n, k, L, _ptr(A), _ptr(B), _ptr(C), ctypes.byref(o)), "mdgemm_ex")

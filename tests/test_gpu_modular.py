@@ -160,6 +160,26 @@ def test_library_buffer_capture_and_a_small_workspace():
         assert torch.equal(C, md.mdgemm_ex(A, B, flags=md.MDGEMM_STAGED))
 
 
+def test_memory_for_the_fp64_products_only(monkeypatch):
+    """Where the larger workspace of the int8 products does not fit the memory, the product runs in
+    the FP64 one (here the allocator's refusal of the larger size is played)."""
+    m, n, k, L = 4096, 40, 500, 4
+    A, B = _operands(L, m, n, k, 13)
+    want = md.mdgemm_ex(A, B, flags=md.MDGEMM_STAGED)
+    plain = md.mdgemm_workspace_bytes(m, n, k, L)
+    full = md.mdgemm_workspace_bytes(m, n, k, L, flags=md.MDGEMM_WORKSPACE_SCRATCH)
+    assert plain < full
+    empty = torch.empty
+
+    def limited(*size, **kw):
+        if size and size[0] == full:
+            raise torch.OutOfMemoryError("played")
+        return empty(*size, **kw)
+
+    monkeypatch.setattr(md.torch, "empty", limited)
+    assert torch.equal(md.mdgemm_ex(A, B), want)
+
+
 @pytest.mark.parametrize("L,m,n,k,opts", [
     (2, 1283, 1409, 130, {}), (2, 1100, 900, 257, {"cutoff": ALL}), (3, 1025, 1023, 127, {}),
     (2, 1409, 1283, 300, {"slice_bits": 20}), (2, 1409, 1500, 200, {"slice_bits": 21}),
