@@ -452,7 +452,7 @@ double staged_estimate_us(int64_t m, int64_t n, int64_t k, int T, int heaviest_p
 }
 
 bool small_plan(int64_t m, int64_t n, int64_t k, int limbs, const Resolved& r, int* kc_out,
-                mdg::SmallLevelOwners* owners, double* fused_us = nullptr) {
+                mdg::SmallLevelOwners* owners, int* simd_pairs = nullptr) {
   if (r.kind == Kind::kGroups ||
       (r.flags & (MDGEMM_INT8 | MDGEMM_KARATSUBA | MDGEMM_KARATSUBA_MIN_TERMS | MDGEMM_STAGED | MDGEMM_CHECK_FINITE)))
     return false;
@@ -485,9 +485,8 @@ bool small_plan(int64_t m, int64_t n, int64_t k, int limbs, const Resolved& r, i
     total += bp;
   }
   const int maxload = std::max(std::max(load[0], load[1]), std::max(load[2], load[3]));
-  const double us = fused_estimate_us(k, limbs, r.S, maxload);
-  if (us > staged_estimate_us(m, n, k, r.T, heaviest, total)) return false;
-  if (fused_us) *fused_us = us;
+  if (fused_estimate_us(k, limbs, r.S, maxload) > staged_estimate_us(m, n, k, r.T, heaviest, total)) return false;
+  if (simd_pairs) *simd_pairs = maxload;
   int kc = static_cast<int>(std::min<int64_t>(256, (k + 3) / 4 * 4));
   while (kc > 4 && mdg::small_product_lds(r.S, r.T, kc) > mdg::kSmallMaxLds) kc -= 4;
   if (mdg::small_product_lds(r.S, r.T, kc) > mdg::kSmallMaxLds) return false;
@@ -500,16 +499,65 @@ bool small_plan(int64_t m, int64_t n, int64_t k, int limbs, const Resolved& r, i
 // afterwards (scratch: the library's buffer, the fixed scratch array, or a caller
 // workspace marked MDGEMM_WORKSPACE_SCRATCH) and the estimated time is below that
 // of the path that would run otherwise.  Not with MDGEMM_STAGED, the shortest
-// Karatsuba schedule, grouped or int8-digit products.
-constexpr double kModularBaseUs = 48.0;  // its launches and their gaps
-// The products of int8 digits level by level (MDGEMM_INT8): every pair one product,
-// an int32 plane per level, and splits that store single bytes (1.0 ps per panel byte
-// measured at 3001 x 4097 x 2999, 15 digits).
-double int8_estimate_us(int64_t m, int64_t n, int64_t k, int S, int T) {
+// Karatsuba schedule or grouped products.
+//
+// The times compared, in microseconds, fitted to every other one of 2179 products measured
+// on every path on MI355X (1 to 16 limbs, 5- to 26-bit digits, int8 digits among them,
+// every cutoff, outputs from 1 x 1 to 6000 x 6000, k up to 6000): of the others nine in ten
+// lie within 0.78 to 1.23 of their time.  For small products and many limbs the terms
+// besides the products decide: each panel and each plane is a step of a serial chain of loads
+// and integer work, whatever the size.  (With one constant of 48 us in their place, 194 of
+// the 1326 products that went to residues were slower there, by up to 2.4 times: 11 limbs
+// 25 x 2 x 8, of 280 panels and planes, 284 us against 148.  Now it is 49 of 1231, by up to
+// 1.4 times.)
+//  residues: the chain of the split (the integer's words; its panels per block; a rate
+//   per limb of the operands), that of the accumulation (its words and planes), and the
+//   plan's own seconds;
+//  fused: MFMAs of the most loaded SIMD, limbs of a tile's lines in rounds of 512 threads,
+//   levels, chunks of 256 values of k; preferred by 5 us, being one launch of six (2 of
+//   the products then lose by the choice, 10 without);
+//  staged: launches, a chain per limb and level, panels and planes at their rates, the level
+//   GEMM of staged_estimate_us;
+//  int8 levels: every pair one product, an int32 plane per level, splits that store single
+//   bytes; the heaviest level's pairs are shared by two blocks where it bounds the time.
+double modular_time_us(int64_t m, int64_t n, int64_t k, int limbs, const Resolved& r, const mdg::ModPlan& pl) {
+  const int bits = r.w * r.S, words = (bits + 52 + 63) / 64, sum = mdg::accum_words(r.T + 1, r.w);
+  const bool brief = mdg::mod_split_short(limbs, bits);
+  const int64_t tiles = mdg::mod_split_tiles(m, n) * ((mdg::mod_kp(k) + 63) / (brief ? 128 : 64));
+  const double values = static_cast<double>(m + n) * static_cast<double>(k) * limbs;
+  double split, per_value;  // of a block's chain and, in picoseconds, of every limb
+  if (brief)
+    split = limbs <= 2 && bits <= 128 ? 14.2 : 17.3, per_value = 6.0;
+  else if (words <= 8 && limbs <= 8)
+    split = limbs <= 4 ? 24.5 : 33.9, per_value = 11.0;
+  else
+    split = 99.0, per_value = 24.0;
+  const double accum = sum <= 3 ? 0.0 : sum <= 5 ? 2.4 : sum <= 8 ? 6.7 : 16.6;
+  return split + 0.35 * std::max(pl.pa, pl.pb) / static_cast<double>(mdg::mod_split_shares(tiles)) +
+         1e-6 * per_value * values + accum + 0.195 * pl.directs + 3.0 * pl.channels + 1e6 * pl.seconds;
+}
+double fused_time_us(int64_t m, int64_t n, int64_t k, int limbs, int T, int simd_pairs) {
+  const int64_t chunks = (k + 255) / 256;
+  const int64_t elements = (std::min<int64_t>(m, 16) + std::min<int64_t>(n, 16)) * std::min<int64_t>(k, 256);
+  const int64_t rounds = (elements + 511) / 512 * chunks;
+  return 1.9 * kMfmaUs * simd_pairs * static_cast<double>((k + 3) / 4) + 0.49 * limbs * static_cast<double>(rounds) +
+         0.234 * (T + 1) + 1.42 * limbs + 5.83 * static_cast<double>(chunks) - 5.0;
+}
+double staged_time_us(int64_t m, int64_t n, int64_t k, int limbs, const Resolved& r) {
+  const double mn = static_cast<double>(m) * static_cast<double>(n);
+  const double elements = static_cast<double>(m + n) * static_cast<double>(k);
+  const double gemm = staged_estimate_us(m, n, k, r.T, max_pairs(r.S, r.T), pair_count(r.S, r.T)) - 57.0;
+  return 13.4 + 0.51 * (r.T + 1) + 3.03 * limbs + (r.w * r.S + 52 > 512 ? 18.9 : 0.0) +
+         elements * (8.0 * limbs + 4.0 * r.S) / 1.17e6 + mn * 16.0 * (r.T + 1) / 6.06e6 + 1.036 * gemm;
+}
+double int8_time_us(int64_t m, int64_t n, int64_t k, int limbs, const Resolved& r) {
   const double mt = static_cast<double>(mdg::i8_rows(m)), nt = static_cast<double>(mdg::i8_rows(n));
   const double kp = static_cast<double>(mdg::i8_kp(k)), mn = static_cast<double>(m) * static_cast<double>(n);
-  return 55.0 + 1e6 * (2.0 * mt * nt * kp * pair_count(S, T) / 2.6e15 + (T + 1) * 8.0 * mn / 4.5e12 +
-                       1.0e-12 * S * static_cast<double>(m + n) * static_cast<double>(k));
+  const double elements = static_cast<double>(m + n) * static_cast<double>(k);
+  const double spread = 2.0 * mt * nt * kp * pair_count(r.S, r.T) / 2.6e9;
+  const double heaviest = 2.0 * 65536.0 * kp * max_pairs(r.S, r.T) / (2.6e9 / 256.0);
+  return 21.4 + 0.08 * (r.T + 1) + 0.21 * r.S + 5.5 * limbs + elements * (6.8e-6 + 4.1e-6 * limbs) +
+         8.0 * (r.T + 1) * mn / 5.4e6 + std::max(spread, 0.55 * heaviest);
 }
 std::shared_ptr<const mdg::ModPlan> modular_for(int64_t m, int64_t n, int64_t k, int limbs, const Resolved& r,
                                                 bool scratch) {
@@ -523,12 +571,12 @@ std::shared_ptr<const mdg::ModPlan> modular_for(int64_t m, int64_t n, int64_t k,
     return nullptr;
   int kc = 0;
   mdg::SmallLevelOwners owners{};
-  double us = 0.0;
-  if (r.flags & MDGEMM_INT8)
-    us = int8_estimate_us(m, n, k, r.S, r.T);
-  else if (!small_plan(m, n, k, limbs, r, &kc, &owners, &us))
-    us = staged_estimate_us(m, n, k, r.T, max_pairs(r.S, r.T), pair_count(r.S, r.T));
-  return kModularBaseUs + 1e6 * pl->seconds < us ? pl : nullptr;
+  int simd_pairs = 0;
+  const double us = (r.flags & MDGEMM_INT8) ? int8_time_us(m, n, k, limbs, r)
+                    : small_plan(m, n, k, limbs, r, &kc, &owners, &simd_pairs)
+                        ? fused_time_us(m, n, k, limbs, r.T, simd_pairs)
+                        : staged_time_us(m, n, k, limbs, r);
+  return modular_time_us(m, n, k, limbs, r, *pl) < us ? pl : nullptr;
 }
 
 // EA | EB | A's panels | B's panels | output planes, each aligned to 256 bytes.

@@ -81,7 +81,9 @@ struct ModPlan {
   int planes = 0;        // dwords per four rows of all output planes
   int direct_bits = 0;   // w
   int64_t products = 0;  // int8 products of length k
-  double seconds = 0.0;  // estimated time, for choosing the path
+  int directs = 0;       // planes of the direct groups
+  int channels = 0;      // sixteens of planes of the residue groups
+  double seconds = 0.0;  // of products, panels and planes at their rates, for choosing the path
 };
 
 // Levels in place: where the level planes G_t themselves are wanted (a caller
@@ -119,6 +121,15 @@ bool modular_accum_fits(const ModPlan& pl, int w);
 bool modular_split_fits(int64_t m, int64_t n, int64_t k);
 
 constexpr int kModMaxWords = 15;  // 64-bit words of the accumulated integer
+
+// The split's tiles: 16 lines by 128 values of k where the integer of an element is short,
+// else 64; the panels of a tile are shared over up to eight blocks.
+constexpr int kModSplitLines = 16;
+inline bool mod_split_short(int L, int bits) { return (L <= 2 && bits <= 128) || (L <= 4 && bits <= 256); }
+inline int64_t mod_split_tiles(int64_t m, int64_t n) {
+  return (m + kModSplitLines - 1) / kModSplitLines + (n + kModSplitLines - 1) / kModSplitLines;
+}
+inline int64_t mod_split_shares(int64_t tiles) { return tiles >= 512 ? 1 : tiles > 64 ? 512 / tiles : 8; }
 
 inline int64_t mod_kp(int64_t k) { return (k + kModStage - 1) / kModStage * kModStage; }
 inline int64_t mod_rows(int64_t x) { return (x + kModTile - 1) / kModTile * kModTile; }

@@ -216,6 +216,7 @@ bool build(const std::vector<Rect>& rects, int64_t longest, int64_t k, int S, in
         pl->jobs.push_back(job);
         pl->products += static_cast<int64_t>(segs.size());
       }
+      (direct ? pl->directs : pl->channels) += direct ? count : (count + 15) / 16;
       pl->planes += count * unit;
       i = j;
       if (pl->pa > kModMaxPanels || pl->pb > kModMaxPanels || pl->planes > 4096 ||
@@ -231,7 +232,14 @@ bool build(const std::vector<Rect>& rects, int64_t longest, int64_t k, int S, in
   return true;
 }
 
-double estimate(const ModPlan& pl, int64_t m, int64_t n, int64_t k) {
+// kCover: the cost that covers are compared by, from the rates alone.  kPath: the time
+// that the product is compared with the other paths by, fitted together with the latencies
+// that the caller adds (modular_time_us): one job alone on a CU takes 0.7 of its time
+// beside others, a panel byte 0.2 ps besides what every limb read takes.
+enum class Estimate { kCover, kPath };
+double estimate(const ModPlan& pl, int64_t m, int64_t n, int64_t k, Estimate what) {
+  const double alone = what == Estimate::kPath ? 0.7 : 1.0;
+  const double panel_byte = what == Estimate::kPath ? 0.7 * kPanelByte : kPanelByte;
   const double mt = static_cast<double>(mod_rows(m)), nt = static_cast<double>(mod_rows(n));
   const double mn = static_cast<double>(m) * static_cast<double>(n);
   // the products: the larger of all blocks spread over the CUs and the longest one
@@ -239,12 +247,11 @@ double estimate(const ModPlan& pl, int64_t m, int64_t n, int64_t k) {
   for (const ModJob& j : pl.jobs) {
     const double block = 2.0 * static_cast<double>(mod_kp(k)) * j.nseg / kInt8Rate + kTileJob;
     s += mt * nt * block;
-    longest = std::max(longest, 256.0 * 65536.0 * block);
+    longest = std::max(longest, alone * 256.0 * 65536.0 * block);
   }
   s = std::max(s, longest);
   for (const ModJob& j : pl.jobs) s += mn * (j.mod == kDirectJob ? 8.0 / kPlaneRate : 2.0 / kPlaneRate + 0.3e-12);
-  s += kPanelByte * static_cast<double>(k) * (static_cast<double>(m) * pl.pa + static_cast<double>(n) * pl.pb);
-  return s;
+  return s + panel_byte * static_cast<double>(k) * (static_cast<double>(m) * pl.pa + static_cast<double>(n) * pl.pb);
 }
 
 }  // namespace
@@ -294,6 +301,7 @@ std::shared_ptr<const ModPlan> modular_plan(int64_t m, int64_t n, int64_t k, int
   const double product = 2.0 * static_cast<double>(mod_kp(kc)) / kInt8Rate;
   const double panel = kPanelByte * static_cast<double>(kc) * (1.0 / mc + 1.0 / nc);
   std::shared_ptr<ModPlan> best;
+  double least = 0.0;
   for (int residues = 0; residues < 2; ++residues) {
     // the search grows with S^4: the longest operands are covered directly
     if (residues && S > 36) continue;
@@ -309,10 +317,13 @@ std::shared_ptr<const ModPlan> modular_plan(int64_t m, int64_t n, int64_t k, int
     for (int64_t longest : {int64_t{255}, int64_t{2}}) {
       auto pl = std::make_shared<ModPlan>();
       if (!build(rects, longest, kc, S, T, w, pl.get()) || !modular_accum_fits(*pl, w)) continue;
-      pl->seconds = estimate(*pl, mc, nc, kc);
-      if (!best || pl->seconds < best->seconds) best = pl;
+      const double cost = estimate(*pl, mc, nc, kc, Estimate::kCover);
+      if (best && cost >= least) continue;
+      least = cost;
+      best = pl;
     }
   }
+  if (best) best->seconds = estimate(*best, mc, nc, kc, Estimate::kPath);
   std::lock_guard<std::mutex> lock(cache.mu);
   if (cache.map.size() > 4096) cache.map.clear();
   return cache.map.emplace(key, best).first->second;

@@ -32,7 +32,7 @@
 namespace mdg {
 namespace {
 
-constexpr int kLines = 16;
+constexpr int kLines = kModSplitLines;
 
 __constant__ const ResidueTable kResidueTable = make_residue_table();
 
@@ -291,7 +291,7 @@ hipError_t launch_split_tile(SplitArgs& a, hipStream_t stream) {
     gx += op.tiles;
   }
   const int64_t gy = (a.kp + TK - 1) / TK;
-  const int64_t gz = std::min<int64_t>(8, std::max<int64_t>(1, 512 / (gx * gy)));
+  const int64_t gz = mod_split_shares(gx * gy);
   auto kernel = modular_split_kernel<NW, ML, TK, kWin>;
   if (lds > 64 * 1024) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
@@ -309,8 +309,7 @@ hipError_t launch_split_tile(SplitArgs& a, hipStream_t stream) {
 // of up to 512 threads per 16 lines) and 65535 blocks along y (64 values of k at least).
 bool modular_split_fits(int64_t m, int64_t n, int64_t k) {
   if (m > (int64_t{1} << 30) || n > (int64_t{1} << 30)) return false;
-  const int64_t tiles = (m + kLines - 1) / kLines + (n + kLines - 1) / kLines;
-  return tiles * 512 < (int64_t{1} << 32) && (mod_kp(k) + 63) / 64 <= 65535;
+  return mod_split_tiles(m, n) * 512 < (int64_t{1} << 32) && (mod_kp(k) + 63) / 64 <= 65535;
 }
 
 hipError_t launch_modular_split(int64_t m, int64_t n, int64_t k, int L, int S, int w, const double* A,

@@ -71,7 +71,7 @@ CASES = [
     (8, 300, 300, 7000, {}),
     (4, 258, 260, 16384, {"slice_bits": -1}),
     (2, 300, 300, 5000, {"slice_bits": -1, "range_bits": 60}),
-    (11, 300, 270, 20, {"slice_bits": -1}),
+    (11, 300, 270, 60, {"slice_bits": -1}),
     # the longest sums of residues and of sub-digits
     (2, 260, 270, 32768, {}),
     (2, 257, 300, 65536, {"slice_bits": 8}),

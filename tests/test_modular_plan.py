@@ -60,7 +60,7 @@ def _options():
     for bits in (24, 60):
         yield f"range {bits}", {"range_bits": bits}
         yield f"range {bits}, adaptive", {"range_bits": bits, "slice_bits": AUTO}
-    for w in (4, 7, 8, 16, 21, 26):
+    for w in (4, 7, 8, 16, 21, 23):
         yield f"{w} bits", {"slice_bits": w}
 
 
@@ -212,3 +212,19 @@ def test_level_passes_stay_below_2_31(probe, w):
         last = (2 ** 31 - 1) // (pairs * c * largest ** 2)  # k of the largest sum below 2^31
         assert probe.probe_level_passes_exact(pairs, last, w)
         assert not probe.probe_level_passes_exact(pairs, last + 1, w)
+
+
+@pytest.mark.parametrize("L,m,n,k,opts,residues", [
+    # measured both ways on MI355X, us by residues and on the path before: each a factor and more apart
+    (11, 25, 2, 8, {"slice_bits": AUTO}, False),                  # 284, 148
+    (16, 157, 11, 11, {"slice_bits": AUTO, "cutoff": 18}, False),  # 281, 183
+    (3, 18, 2730, 2, {}, False),                                  # 73, 54
+    (5, 17, 23, 15, {"cutoff": ALL}, False),                      # 107, 88
+    (2, 64, 64, 64, {"cutoff": ALL}, False),                      # 29, 25
+    (2, 333, 217, 501, {}, True),                                 # 61, 291
+    (3, 55, 5623, 3157, {"flags": md.MDGEMM_INT8}, True),         # 1231, 1533
+    (2, 783, 35, 1505, {"flags": md.MDGEMM_INT8}, True),          # 84, 159
+    (2, 4096, 4096, 4096, {}, True),
+])
+def test_the_faster_path_is_chosen(L, m, n, k, opts, residues):
+    assert (_chosen(m, n, k, L, opts) is not None) == residues
