@@ -114,7 +114,10 @@ def test_limbs_equal_the_oracle(L, m, n, k, opts):
 
 
 @pytest.mark.parametrize("m,n,k,opts", [(260, 258, 512, {}), (260, 258, 512, {"cutoff": ALL}),
-                                        (260, 258, 512, {"slice_bits": 20}), (1000, 1000, 400, {"slice_bits": 21})])
+                                        (260, 258, 512, {"slice_bits": 20}), (1000, 1000, 400, {"slice_bits": 21}),
+                                        # the longest sums of residues (2^15 terms) and of sub-digits (2^16)
+                                        (260, 258, 32768, {}), (260, 258, 32768, {"cutoff": ALL}),
+                                        (260, 258, 65536, {"slice_bits": 8})])
 def test_largest_digits_of_either_sign(m, n, k, opts):
     """Every digit at its largest magnitude: the sums reach their bounds."""
     print(f"[case] largest digits {m}x{n}x{k} {opts}", flush=True)
@@ -187,6 +190,8 @@ def test_memory_for_the_fp64_products_only(monkeypatch):
     # a last tile of few elements: one to three rows of 1 to 40 columns
     (1, 4097, 1, 256, {}), (1, 4097, 17, 256, {}), (1, 4098, 9, 256, {}), (1, 4099, 40, 256, {}),
     (2, 4097, 33, 384, {}),
+    # four sub-digits (the int8 panels fit the digit panels' room at whole stages of k), longer k
+    (2, 2550, 2500, 256, {"slice_bits": 21}), (4, 1100, 1000, 2048, {}),
 ])
 def test_a_readable_workspace_holds_digits_and_levels(L, m, n, k, opts):
     """Without MDGEMM_WORKSPACE_SCRATCH the workspace holds the exponents, digit panels and
