@@ -202,7 +202,7 @@ typedef struct mdgemm_opts {
  * products run this way too where nothing reads the workspace and it is estimated
  * faster.
  * Not with MDGEMM_STAGED, MDGEMM_KARATSUBA_MIN_TERMS or the grouped products, nor for
- * k above 2^15.
+ * k above 2^16 (by residues 2^15).
  * In a workspace that may be read, the pair schedule's levels are formed one by one
  * on the int8 matrix cores over 7-bit sub-digits where that is estimated faster; the
  * workspace then holds the same exponents, digits and levels. */
