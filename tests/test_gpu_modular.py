@@ -163,6 +163,33 @@ def test_library_buffer_capture_and_a_small_workspace():
         assert torch.equal(C, md.mdgemm_ex(A, B, flags=md.MDGEMM_STAGED))
 
 
+@pytest.mark.parametrize("L,m,n,k,flags", [
+    (8, 300, 280, 150, md.MDGEMM_WORKSPACE_SCRATCH),   # the split's integers in more than 64 KB of LDS
+    (16, 260, 270, 40, md.MDGEMM_WORKSPACE_SCRATCH),   # two launches of the products
+    (2, 1100, 1300, 200, 0),                           # levels in a readable workspace
+    (8, 520, 700, 100, 0),
+])
+def test_capture_of_every_kernel_form(L, m, n, k, flags):
+    A, B = _operands(L, m, n, k, 31)
+    ws = torch.empty(md.mdgemm_workspace_bytes(m, n, k, L, flags=flags), dtype=torch.uint8, device=DEV)
+    C = torch.empty((L, m, n), dtype=torch.float64, device=DEV)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        md.mdgemm_ex(A, B, C, workspace=ws, flags=flags)
+    torch.cuda.current_stream().wait_stream(side)
+    for rep in range(3):
+        print(f"[case] L={L} {m}x{n}x{k} flags={flags} graph replay {rep}", flush=True)
+        A2, B2 = _operands(L, m, n, k, 40 + rep)
+        A.copy_(A2)
+        B.copy_(B2)
+        C.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(C, md.mdgemm_ex(A, B, flags=md.MDGEMM_STAGED))
+
+
 def test_memory_for_the_fp64_products_only(monkeypatch):
     """Where the larger workspace of the int8 products does not fit the memory, the product runs in
     the FP64 one (here the allocator's refusal of the larger size is played)."""
