@@ -747,8 +747,9 @@ Cache& cache() {
   return c;
 }
 
-// With c.mu held: the buffer of the current device, grown to `need` bytes.
-int cached_workspace(Cache& c, size_t need, void** out, int* dev_out) {
+// With c.mu held: the buffer of the current device, grown to `need` bytes.  keep: where
+// the free memory does not hold that, MDGEMM_ENOMEM and the buffer stays as it is.
+int cached_workspace(Cache& c, size_t need, bool keep, void** out, int* dev_out) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return MDGEMM_EHIP;
   *dev_out = dev;
@@ -762,6 +763,8 @@ int cached_workspace(Cache& c, size_t need, void** out, int* dev_out) {
     return MDGEMM_EHIP;
   }
   if (c.bytes[dev] < need) {
+    size_t free = 0, total = 0;
+    if (keep && hipMemGetInfo(&free, &total) == hipSuccess && free + c.bytes[dev] < need) return MDGEMM_ENOMEM;
     if (c.ptr[dev]) {
       if (hipDeviceSynchronize() != hipSuccess) return MDGEMM_EHIP;
       (void)hipFree(c.ptr[dev]);
@@ -789,14 +792,16 @@ int cached_workspace(Cache& c, size_t need, void** out, int* dev_out) {
 class LibraryBuffer {
  public:
   ~LibraryBuffer() { release(MDGEMM_OK); }
-  int acquire(size_t need, hipStream_t stream, char** out) {
+  // keep: give up (MDGEMM_ENOMEM) rather than free the buffer for one that cannot be
+  // had, for a caller that takes a smaller one then
+  int acquire(size_t need, hipStream_t stream, char** out, bool keep = false) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cap) != hipSuccess) return MDGEMM_EHIP;
     if (cap != hipStreamCaptureStatusNone) return MDGEMM_EINVAL;
     lock_ = std::unique_lock<std::mutex>(cache().mu);
     void* p = nullptr;
     int dev = -1;
-    const int st = cached_workspace(cache(), need, &p, &dev);
+    const int st = cached_workspace(cache(), need, keep, &p, &dev);
     if (st != MDGEMM_OK) {
       lock_.unlock();
       return st;
@@ -1124,7 +1129,7 @@ int ex_impl(int64_t m, int64_t n, int64_t k, int limbs, const double* A, const d
       if (workspace_overlaps(opts->workspace, lm.total, m, n, k, limbs, A, B, C)) return MDGEMM_EINVAL;
       ws = static_cast<char*>(opts->workspace);
     } else {
-      st = lib.acquire(lm.total, s, &ws);
+      st = lib.acquire(lm.total, s, &ws, true);
     }
     if (st == MDGEMM_OK) {
       MDG_TRY(lib.release(enqueue_modular(m, n, k, limbs, A, B, C, r, *mod, lm, ws)));

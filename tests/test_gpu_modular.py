@@ -8,6 +8,8 @@ rows of four that the planes hold; the options cover every sub-digit count, resi
 systems of one to three limb chunks, and the word counts of the accumulation.
 """
 
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -316,6 +318,35 @@ def test_stage_times_of_levels_on_int8():
     staged, int8 = times[md.MDGEMM_STAGED], times[0]
     assert int8[2] < 0.5 * staged[2]  # the levels did run on the int8 matrix cores
     assert int8[3] < 2.0 * staged[3] and int8[1] > staged[1], times
+
+
+def test_library_buffer_that_cannot_grow():
+    """A product whose int8 panels exceed the card's memory runs on FP64 in the library's buffer, which
+    is neither freed nor waited for on the way: only the first call takes time on the host."""
+    L, m, n, k = 4, 18 << 20, 16, 16
+    total = torch.cuda.get_device_properties(0).total_memory
+    if md.mdgemm_workspace_bytes(m, n, k, L, flags=md.MDGEMM_WORKSPACE_SCRATCH) < total or total < 200 << 30:
+        pytest.skip("the panels fit, or the FP64 ones do not")
+    torch.cuda.empty_cache()
+    A = torch.zeros(L, m, k, dtype=torch.float64, device=DEV)
+    A[0] = 1.5
+    A[1] = 2.0 ** -60
+    A[0, :, 3] = torch.arange(m, dtype=torch.float64, device=DEV)
+    B, _ = _operands(L, k, 2, n, 3)
+    host = []
+    for rep in range(4):
+        print(f"[case] library buffer {m}x{n}x{k}, call {rep}", flush=True)
+        torch.cuda.synchronize()
+        start = time.perf_counter()
+        C = md.mdgemm(A, B)
+        host.append(time.perf_counter() - start)
+    torch.cuda.synchronize()
+    rows = slice(m - 1000, m)
+    assert torch.equal(C[:, rows], md.mdgemm_ex(A[:, rows].contiguous(), B, flags=md.MDGEMM_STAGED))
+    del A, C
+    torch.cuda.empty_cache()
+    md.mdgemm_release()
+    assert max(host[1:]) < 0.1, host
 
 
 def _least(total, shapes):
