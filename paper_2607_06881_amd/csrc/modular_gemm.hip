@@ -160,7 +160,8 @@ __global__ void __launch_bounds__(512, 1) modular_levels_kernel(int64_t m, int64
         for (int r = 0; r < 4; ++r)
 #pragma unroll
           for (int y = 0; y < 4; ++y)
-            old[r][y] = __builtin_amdgcn_raw_buffer_load_b64(rg, (y < cols ? off + r * pitch : kOutside) + 128 * y, 0, 0);
+            old[r][y] =
+                __builtin_amdgcn_raw_buffer_load_b64(rg, (y < cols ? off + r * pitch : kOutside) + 128 * y, 0, 0);
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r)

@@ -324,8 +324,9 @@ __global__ void __launch_bounds__(256) qr_pack_v_kernel(int64_t m, int64_t n, in
 // of all kMaxNb x kMaxNb entries, kGramShare of them per workgroup (grid.y): bound by
 // the FP64 instructions of the few waves in flight, 40 us with all entries in one
 // workgroup at 2048 rows (64 workgroups, 16 entries a thread one after the other), now
-// 12 us (2048 x 2048 QR 27.0 -> 26.1 ms); the staging that is repeated is small.  A second launch (one thread per entry)
-// adds the partials of each entry in workgroup order and writes G [2][jb][jb].
+// 12 us (2048 x 2048 QR 27.0 -> 26.1 ms); the staging that is repeated is small.  A
+// second launch (one thread per entry) adds the partials of each entry in workgroup
+// order and writes G [2][jb][jb].
 constexpr int kGramRows = 32;
 constexpr int kGramShare = 512;
 static_assert(kMaxNb * kMaxNb % kGramShare == 0 && kGramShare % kColThreads == 0, "whole workgroups of entries");
@@ -653,8 +654,8 @@ int qr_core(int64_t m, int64_t nf, int64_t n, int nb, double* A, double* tau, vo
     // G = V^T V (double-double dot products over the panel's rows)
     const unsigned ggroups = static_cast<unsigned>((mp + mdg::kGramRows - 1) / mdg::kGramRows);
     hipLaunchKernelGGL(mdg::qr_gram_partial_kernel,
-                       dim3(ggroups, mdg::kMaxNb * mdg::kMaxNb / mdg::kGramShare), dim3(mdg::kColThreads), 0, s, m, n, j0, jb, A,
-                       pgram);
+                       dim3(ggroups, mdg::kMaxNb * mdg::kMaxNb / mdg::kGramShare), dim3(mdg::kColThreads), 0, s, m, n,
+                       j0, jb, A, pgram);
     hipLaunchKernelGGL(mdg::qr_gram_reduce_kernel, dim3(mdg::kMaxNb * mdg::kMaxNb / mdg::kGramThreads),
                        dim3(mdg::kGramThreads), 0, s, jb, static_cast<int64_t>(ggroups), pgram, G);
     if (hipGetLastError() != hipSuccess) return MDGEMM_EHIP;

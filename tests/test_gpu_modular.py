@@ -287,7 +287,8 @@ def test_a_readable_int8_workspace_holds_digits_and_levels(L, m, n, k, opts):
         off += up(size, 256)
     untouched = bool((ws[need:] == 0x5a).all())  # not in the assert, whose report would walk the tensor
     assert off == need and untouched
-    assert torch.equal(parts["EA"].view(torch.int32), want["EA"]) and torch.equal(parts["EB"].view(torch.int32), want["EB"])
+    assert torch.equal(parts["EA"].view(torch.int32), want["EA"])
+    assert torch.equal(parts["EB"].view(torch.int32), want["EB"])
     da = parts["DA"].view(torch.int8).view(mp, pitch)[:m, 128:].reshape(m, S, kp)[:, :, :k]
     assert torch.equal(da.to(torch.float32), want["DA"][:S, :k, :m].to(torch.float32).permute(2, 0, 1))
     levels = parts["G"].view(torch.int32).view(T + 1, m, n)

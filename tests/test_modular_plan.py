@@ -164,8 +164,9 @@ def _value(pl, moduli, A, B, w):
 
 
 @pytest.mark.parametrize("m,n,k,S,T,w", [
-    (4096, 4096, 4096, 8, 7, 13), (300, 300, 700, 8, 14, 13), (2048, 2048, 1024, 16, 15, 13), (500, 500, 40, 34, 33, 13),
-    (300, 300, 1500, 66, 65, 13), (300, 300, 7000, 34, 33, 13), (300, 300, 3000, 34, 66, 13), (300, 300, 16384, 11, 10, 20),
+    (4096, 4096, 4096, 8, 7, 13), (300, 300, 700, 8, 14, 13), (2048, 2048, 1024, 16, 15, 13),
+    (500, 500, 40, 34, 33, 13), (300, 300, 1500, 66, 65, 13), (300, 300, 7000, 34, 33, 13),
+    (300, 300, 3000, 34, 66, 13), (300, 300, 16384, 11, 10, 20),
     (128, 8192, 64, 66, 65, 13), (900, 900, 30000, 15, 14, 7), (400, 400, 300, 3, 2, 26), (400, 400, 300, 5, 8, 21),
     (200, 200, 2000, 20, 3, 5), (300, 300, 32768, 4, 3, 13), (300, 300, 50000, 13, 12, 8), (300, 300, 9, 1, 0, 13),
     (300, 300, 200, 36, 40, 16), (300, 300, 200, 12, 20, 9),
